@@ -63,16 +63,45 @@ __device__ __forceinline__ size_t anode(int x, int y, int z, int nx, int ny) {
 // The adjoints of the next time level, gathered along the streaming: population q of node x went
 // to x + c_q, so its adjoint is lam_next[q] there.
 template <Addr A, typename R>
-__device__ __forceinline__ void gather_next(const R* lam_next, size_t n, const Rows& rw, const Planes& pl,
-                                            R (&mf)[kQ], R (&mg)[kM]) {
+__device__ __forceinline__ void gather_next_fluid(const R* lam_next, size_t n, const Rows& rw, const Planes& pl,
+                                                  R (&l)[kQ]) {
 #pragma unroll
   for (int i = 0; i < kQ; ++i)
-    mf[i] = ld<A>(lam_next + static_cast<size_t>(i) * n, rw.at(cq(i, 0), cq(i, 1)) + pl.at(cq(i, 2)));
+    l[tidx(cq(i, 0) + 1, cq(i, 1) + 1, cq(i, 2) + 1)] =
+        ld<A>(lam_next + static_cast<size_t>(i) * n, rw.at(cq(i, 0), cq(i, 1)) + pl.at(cq(i, 2)));
+}
+template <Addr A, typename R>
+__device__ __forceinline__ void gather_next_magnetic(const R* lam_next, size_t n, const Rows& rw, const Planes& pl,
+                                                     R (&mg)[kM]) {
 #pragma unroll
   for (int i = 0; i < 7; ++i) {
     const uint32_t dn = rw.at(xim(i, 0), xim(i, 1)) + pl.at(xim(i, 2));
 #pragma unroll
     for (int c = 0; c < 3; ++c) mg[i * 3 + c] = ld<A>(lam_next + static_cast<size_t>(kQ + i * 3 + c) * n, dn);
+  }
+}
+
+// The reverse pass of one node from its forward quantities: gathers the next adjoints, writes the
+// node's (and, on the stencil route, lJ).
+template <Addr A, typename R, bool MOMENT>
+__device__ __forceinline__ void reverse_node(const VjpState<R>& fw, const R (&F)[3], const PhysConst<R>& k,
+                                             const R* lam_next, R* lam, R* lam_j, size_t n, const Rows& rw,
+                                             const Planes& pl, uint32_t cell) {
+  NodeAdjoint<R> o;
+  R l[kQ];
+  gather_next_fluid<A>(lam_next, n, rw, pl, l);
+  vjp_fluid(fw, F, k, l, o);
+  R mg[kM], lJ[3];
+  gather_next_magnetic<A>(lam_next, n, rw, pl, mg);
+  vjp_magnetic<R, MOMENT>(fw, k, o, mg, lJ);
+  vjp_fluid_populations(fw, o, l);
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) st<A>(lam + static_cast<size_t>(q) * n, cell, l[q]);
+#pragma unroll
+  for (int q = 0; q < kM; ++q) st<A>(lam + static_cast<size_t>(kQ + q) * n, cell, mg[q]);
+  if (!MOMENT) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) st<A>(lam_j + static_cast<size_t>(c) * n, cell, lJ[c]);
   }
 }
 
@@ -104,18 +133,7 @@ __global__ FLAME_ADJ_BOUNDS void adjoint_step_kernel(AdjArgs<R> a) {
     fw = vjp_forward<R, MOMENT>(f, g, F, S, J, a.k);
   }
   adj_phase_fence();
-  R mf[kQ], mg[kM];
-  gather_next<A>(a.lam_next, n, rw, pl, mf, mg);
-  R lf[kQ], lg[kM], lJ[3];
-  vjp_reverse<R, MOMENT>(fw, F, a.k, mf, mg, lf, lg, lJ);
-#pragma unroll
-  for (int q = 0; q < kQ; ++q) st<A>(a.lam + static_cast<size_t>(q) * n, cell, lf[q]);
-#pragma unroll
-  for (int q = 0; q < kM; ++q) st<A>(a.lam + static_cast<size_t>(kQ + q) * n, cell, lg[q]);
-  if (!MOMENT) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) st<A>(a.lam_j + static_cast<size_t>(c) * n, cell, lJ[c]);
-  }
+  reverse_node<A, R, MOMENT>(fw, F, a.k, a.lam_next, a.lam, a.lam_j, n, rw, pl, cell);
 }
 
 // Moment route from a trace lattice: the step's pre-collision state is the lattice pulled.
@@ -171,14 +189,7 @@ __global__ FLAME_ADJ_BOUNDS void adjoint_trace_kernel(AdjTraceArgs<S> a) {
     fw = vjp_forward<R, true>(f, g, F, Sb, unused, a.k);
   }
   adj_phase_fence();
-  R mf[kQ], mg[kM];
-  gather_next<A>(a.lam_next, n, rw, pl, mf, mg);
-  R lf[kQ], lg[kM], lJ[3];
-  vjp_reverse<R, true>(fw, F, a.k, mf, mg, lf, lg, lJ);
-#pragma unroll
-  for (int q = 0; q < kQ; ++q) st<A>(a.lam + static_cast<size_t>(q) * n, cell, lf[q]);
-#pragma unroll
-  for (int q = 0; q < kM; ++q) st<A>(a.lam + static_cast<size_t>(kQ + q) * n, cell, lg[q]);
+  reverse_node<A, R, true>(fw, F, a.k, a.lam_next, a.lam, static_cast<R*>(nullptr), n, rw, pl, cell);
 }
 
 // Stencil route: b_c of every magnetic population set feeds J of the six face neighbours; add

@@ -139,24 +139,24 @@ struct Zero3 {
 };
 
 // Fluid collision of the model, in place.
-template <int MODEL, bool Grouped, typename R>
+template <int MODEL, bool Separable, typename R>
 __device__ __forceinline__ void collide_fluid_model(R (&f)[kQ], const FluidMoments<R>& m, const R (&U)[3],
                                                     const R (&b)[3], const R (&b0)[3], const R (&F)[3], R omega) {
   if constexpr ((MODEL & kModelBGK) != 0)
     collide_fluid_bgk(f, m, U, b, b0, F, omega);
   else
-    collide_fluid<R, Grouped>(f, m, R(1) + m.drho, U, b, b0, F, omega);
+    collide_fluid<R, Separable>(f, m, R(1) + m.drho, U, b, b0, F, omega);
 }
 
 // Node update from loaded populations and J: moments, both collisions, in place in f and g.
 // Um is the bulk velocity as the magnetic equilibrium sees it (zero for electron MHD).
-template <int MODEL, bool Grouped, typename R>
+template <int MODEL, bool Separable, typename R>
 __device__ __forceinline__ void collide_node(R (&f)[kQ], R (&g)[kM], const FluidMoments<R>& m, const R (&U)[3],
                                              const R (&Um)[3], const R (&b)[3], const R (&J)[3], const R (&F)[3],
                                              const R (&Sb)[3], const PhysConst<R>& k) {
   const R b0[3] = {k.b0[0], k.b0[1], k.b0[2]};
   const R B[3] = {b0[0] + b[0], b0[1] + b[1], b0[2] + b[2]};
-  collide_fluid_model<MODEL, Grouped>(f, m, U, b, b0, F, k.omega);
+  collide_fluid_model<MODEL, Separable>(f, m, U, b, b0, F, k.omega);
   collide_magnetic(g, Um, B, b, J, Sb, k.alpha, k.omega_b);
 }
 
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
   R J[3];
   current_from_moments(lam, Um, B, a.k.alpha, a.k.omega_b, J);
   if (SAVE) save_current<A>(a.save, a.n, cell, J);
-  collide_node<MODEL, sizeof(S) == 2>(f, g, m, U, Um, b, J, F, Sb, a.k);
+  collide_node<MODEL, sizeof(S) != 4>(f, g, m, U, Um, b, J, F, Sb, a.k);
   store_fluid<S, FAA, PAR, A>(a, rw, pl, f);
   store_magnetic<S, MAA, PAR, A>(a, rw, pl, g);
 }
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kTX * Tile<typename Enc<S>::R>::ty, FLAME_ZMARCH_WA
 #pragma unroll
       for (int c = 0; c < 3; ++c) b[c] = b_component(g, c, R(0.5) * Sb[c]);
       const R b0[3] = {a.k.b0[0], a.k.b0[1], a.k.b0[2]};
-      collide_fluid_model<MODEL, false>(f, m, U, b, b0, F, a.k.omega);
+      collide_fluid_model<MODEL, sizeof(S) != 4>(f, m, U, b, b0, F, a.k.omega);
       store_fluid<S, FAA, PAR>(a, rw, pl, f);
     }
     __syncthreads();
