@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "flame_device.h"
+#include "flame_internal.h"
 
 namespace flame {
 
@@ -27,6 +28,15 @@ struct Rows {
       for (int dy = -1; dy <= 1; ++dy)
         r[dx + 1][dy + 1] = static_cast<uint32_t>(wrap(y + dy, ny)) * nx + static_cast<uint32_t>(wrap(x + dx, nx));
   }
+  // from x and the three row offsets y' * nx
+  __device__ __forceinline__ Rows(uint32_t x, uint32_t nx, uint32_t below, uint32_t row, uint32_t above) {
+    const uint32_t xs[3] = {x == 0 ? nx - 1 : x - 1, x, x + 1 == nx ? 0 : x + 1};
+    const uint32_t ys[3] = {below, row, above};
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy) r[dx][dy] = ys[dy] + xs[dx];
+  }
   __device__ __forceinline__ uint32_t at(int dx, int dy) const { return r[dx + 1][dy + 1]; }
 };
 
@@ -36,7 +46,6 @@ struct Rows {
 // per array (base in scalar registers, no range limit below 4 GiB, raw addressing) and the 32-bit
 // offset as the only per-lane operand, which takes the 64-bit address arithmetic off the vector
 // ALU (about 140 of the node-local step's 1240 vector instructions per node at FP16 storage).
-// Non-temporal stores unless FLAME_NT_STORES is 0.
 enum class Addr { Global, Buffer };
 typedef unsigned int U32x2 __attribute__((ext_vector_type(2)));
 template <typename S>
@@ -58,11 +67,13 @@ __device__ __forceinline__ S ld(const S* base, uint32_t off) {
     return *reinterpret_cast<const S*>(reinterpret_cast<const char*>(base) + vo);
   }
 }
-template <Addr A, typename S>
+// NT: with the non-temporal hint (unless FLAME_NT_STORES is 0).
+template <Addr A, bool NT = true, typename S>
 __device__ __forceinline__ void st(S* base, uint32_t off, S v) {
+  constexpr bool nt = NT && FLAME_NT_STORES;
   const uint32_t vo = off * static_cast<uint32_t>(sizeof(S));
   if constexpr (A == Addr::Buffer) {
-    constexpr int aux = FLAME_NT_STORES ? 2 : 0;   // 2: the non-temporal hint
+    constexpr int aux = nt ? 2 : 0;   // 2: the non-temporal hint
     if constexpr (sizeof(S) == 2)
       __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, v), rsrc_of(base), vo, 0, aux);
     else if constexpr (sizeof(S) == 4)
@@ -71,16 +82,17 @@ __device__ __forceinline__ void st(S* base, uint32_t off, S v) {
       __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U32x2, v), rsrc_of(base), vo, 0, aux);
   } else {
     S* p = reinterpret_cast<S*>(reinterpret_cast<char*>(base) + vo);
-    if (FLAME_NT_STORES)
+    if (nt)
       __builtin_nontemporal_store(v, p);
     else
       *p = v;
   }
 }
 
-// Plane offsets of z - 1, z, z + 1 (periodic), uniform across the workgroup.
+// Plane offsets of z - 1, z, z + 1 (periodic).
 struct Planes {
   uint32_t p[3];
+  __device__ __forceinline__ Planes(uint32_t below, uint32_t here, uint32_t above) : p{below, here, above} {}
   __device__ __forceinline__ Planes(int z, int nz, uint32_t plane) {
     p[0] = static_cast<uint32_t>(wrap(z - 1, nz)) * plane;
     p[1] = static_cast<uint32_t>(z) * plane;
@@ -88,6 +100,40 @@ struct Planes {
   }
   __device__ __forceinline__ uint32_t at(int dz) const { return p[dz + 1]; }
 };
+
+// The node-local kernels split the grid by linear node index: a block owns g.threads consecutive
+// nodes, whatever the row length, so every lane of every wavefront but the grid's last has a node
+// and a block's own accesses start on a whole cache line also where the rows do not (a row per
+// block leaves 16% of the lanes idle at nx = 161 and straddles a line at both ends of every wavefront).
+// The division by nx and by the plane is a multiplication by floor(2^32 / d), one short at most.
+__device__ __forceinline__ uint32_t div_by(uint32_t t, Divisor d, uint32_t& rest) {
+  uint32_t q = __umulhi(t, d.inv);
+  rest = t - q * d.d;
+  if (rest >= d.d) {
+    ++q;
+    rest -= d.d;
+  }
+  return q;
+}
+struct NodeAt {
+  uint32_t cell;
+  Rows rw;
+  Planes pl;
+  static __device__ __forceinline__ NodeAt of(uint32_t cell, const GridShape& g) {
+    uint32_t rem, x;
+    const uint32_t z = div_by(cell, g.plane, rem);
+    const uint32_t y = div_by(rem, g.nx, x);
+    const uint32_t row = rem - x, here = cell - rem, nx = g.nx.d, plane = g.plane.d;
+    return {cell,
+            Rows(x, nx, y == 0 ? plane - nx : row - nx, row, row + nx == plane ? 0 : row + nx),
+            Planes(z == 0 ? g.n - plane : here - plane, here, here + plane == g.n ? 0 : here + plane)};
+  }
+};
+// The node of this thread, or false beyond the grid's end.
+__device__ __forceinline__ bool own_cell(const GridShape& g, uint32_t& cell) {
+  cell = logical_index(g.blocks) * g.threads + threadIdx.x;
+  return cell < g.n;
+}
 
 // Buffer addressing is used when every array the kernel touches ends at least 16 bytes below
 // 4 GiB, so that no access can meet the range limit whichever byte of it the hardware checks.

@@ -406,8 +406,7 @@ FLAME_HD void populate_reverse(R (&l)[kQ], R rho, const R (&U)[3], const R (&Q)[
 // above; false, one direction at a time in the App. A order. The transforms take the step from
 // 1073 to 703 vector instructions and 265 to 172 registers (FP64), the FP16 step at 384^3 from 5.55
 // to 5.04 ms, FP64 at 512^3 from 37.1 to 35.8 ms for an even and an odd step, and their FP32 error against
-// FP64 is 30% smaller. With FP32 storage the odd in-place step keeps the one-at-a-time order, whose stores
-// combine better in L2 (20.9 against 21.6 ms at 512^3).
+// FP64 is 30% smaller.
 template <typename R, bool Separable = false>
 FLAME_HD void collide_fluid(R (&f)[kQ], const FluidMoments<R>& m, R rho,
                                               const R (&U)[3], const R (&b)[3], const R (&b0)[3],

@@ -111,26 +111,42 @@ SetPtrs set_ptrs(const flame_ctx* c);
 #endif
 constexpr unsigned kXCDs = 8;
 
+__device__ __forceinline__ unsigned logical_index(unsigned total) {
+  const unsigned h = blockIdx.x;
+  if (!FLAME_XCD_REMAP) return h;
+  const unsigned q = total / kXCDs, r = total % kXCDs;
+  const unsigned j = h % kXCDs, k = h / kXCDs;
+  return j * q + min(j, r) + k;
+}
 __device__ __forceinline__ void logical_block(unsigned gx, unsigned gy, unsigned gz, unsigned& bx, unsigned& by,
                                               unsigned& bz) {
-  const unsigned total = gx * gy * gz;
-  const unsigned h = blockIdx.x;
-  unsigned l = h;
-  if (FLAME_XCD_REMAP) {
-    const unsigned q = total / kXCDs, r = total % kXCDs;
-    const unsigned j = h % kXCDs, k = h / kXCDs;
-    l = j * q + min(j, r) + k;
-  }
+  const unsigned l = logical_index(gx * gy * gz);
   bx = l % gx;
   by = (l / gx) % gy;
   bz = l / (gx * gy);
 }
 
-// Threads of a row block of the node-local kernels: one row of nx nodes rounded up to whole
-// wavefronts, at most 256 (longer rows take several blocks), so that short rows leave no wave
-// of a block idle.
-// Threads per row block of the node-local kernels, whose launch bounds are 256 threads: never more
-// than that, whatever FLAME_ROW_THREADS asks for.
+// Grid extents of the kernels that split the grid by linear node index, with floor(2^32 / d) for
+// the divisions by a row and by a plane. flame_init refuses grids of 2^32 nodes or more.
+struct Divisor {
+  uint32_t d, inv;
+};
+struct GridShape {
+  Divisor nx, plane;
+  uint32_t n;
+  uint32_t threads, blocks;   // launch shape, as an argument: blockDim is a load that every address waits for
+};
+inline Divisor divisor(uint32_t d) { return {d, static_cast<uint32_t>(std::min<uint64_t>((uint64_t(1) << 32) / d, UINT32_MAX))}; }
+inline GridShape grid_shape(const flame_params& p, unsigned threads) {
+  const size_t n = static_cast<size_t>(p.nx) * p.ny * p.nz;
+  return {divisor(static_cast<uint32_t>(p.nx)), divisor(static_cast<uint32_t>(p.nx) * p.ny), static_cast<uint32_t>(n),
+          threads, static_cast<uint32_t>((n + threads - 1) / threads)};
+}
+
+// Threads per block of the node-local kernels: a row of nx nodes rounded up to whole wavefronts, at
+// most 256 (their launch bound), whatever FLAME_ROW_THREADS asks for. The blocks of the kernels that
+// split the grid by linear node index need not hold whole rows; there short rows only make blocks
+// small, which spreads a small grid over more compute units.
 constexpr int kRowThreadsMax = 256;
 inline unsigned row_threads(int nx) { return static_cast<unsigned>(std::min(kRowThreadsMax, (nx + 63) / 64 * 64)); }
 inline unsigned row_threads(const flame_ctx* c) {

@@ -12,8 +12,8 @@
 // neighbour fields read for curl B are never overwritten during the step.
 //
 // Two kernels:
-//   step_local  - moment-route J: every node independent, one node per thread, rows of up to
-//     256 nodes per block; with FP16 and FP64 storage its arrays are addressed through buffer
+//   step_local  - moment-route J: every node independent, one node per thread, blocks of up to
+//     256 consecutive nodes; with FP16 and FP64 storage its arrays are addressed through buffer
 //     resources when every array ends at least 16 bytes below 4 GiB, otherwise (and with FP32
 //     storage) through 64-bit global addresses (bitwise the same step either way).
 //   step_zmarch - stencil J: a workgroup owns a 64 x 4 tile of (x, y) and marches along z. It
@@ -39,6 +39,7 @@ struct StepArgs {
   const R* force_u;   // [3][n] or null
   const R* force_b;   // [3][n] or null
   int nx, ny, nz;
+  GridShape shape;
   int zchunk;         // planes per workgroup (z-marching kernel)
   size_t n;           // nodes (stride of the caller's forcing arrays)
   size_t stride;      // elements between consecutive population arrays (n plus padding)
@@ -68,7 +69,7 @@ __device__ __forceinline__ void load_fluid(const StepArgs<S>& a, const Rows& rw,
   }
 }
 
-template <typename S, bool FAA, int PAR, Addr A = Addr::Global>
+template <typename S, bool FAA, int PAR, bool NT = true, Addr A = Addr::Global>
 __device__ __forceinline__ void store_fluid(const StepArgs<S>& a, const Rows& rw, const Planes& pl,
                                             const typename Enc<S>::R (&f)[kQ]) {
   using E = Enc<S>;
@@ -78,7 +79,7 @@ __device__ __forceinline__ void store_fluid(const StepArgs<S>& a, const Rows& rw
     const bool shifted = FAA && PAR == 1;
     const uint32_t off = shifted ? rw.at(cq(i, 0), cq(i, 1)) + pl.at(cq(i, 2)) : rw.at(0, 0) + pl.at(0);
     S* base = a.f_dst + static_cast<size_t>(FAA && PAR == 0 ? oppq(i) : i) * a.stride;
-    st<A>(base, off, E::enc(f[i], R(E::fscale(i))));
+    st<A, NT>(base, off, E::enc(f[i], R(E::fscale(i))));
   }
 }
 
@@ -99,7 +100,7 @@ __device__ __forceinline__ void load_magnetic(const StepArgs<S>& a, const Rows& 
   }
 }
 
-template <typename S, bool MAA, int PAR, Addr A = Addr::Global>
+template <typename S, bool MAA, int PAR, bool NT = true, Addr A = Addr::Global>
 __device__ __forceinline__ void store_magnetic(const StepArgs<S>& a, const Rows& rw, const Planes& pl,
                                                const typename Enc<S>::R (&g)[kM]) {
   using E = Enc<S>;
@@ -111,7 +112,7 @@ __device__ __forceinline__ void store_magnetic(const StepArgs<S>& a, const Rows&
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       S* base = a.g_dst + static_cast<size_t>((MAA && PAR == 0 ? oppm(i) : i) * 3 + c) * a.stride;
-      st<A>(base, off, E::enc(g[i * 3 + c], R(E::mscale(i))));
+      st<A, NT>(base, off, E::enc(g[i * 3 + c], R(E::mscale(i))));
     }
   }
 }
@@ -176,21 +177,22 @@ __device__ __forceinline__ void save_current(R* save, size_t n, uint32_t cell, c
 }
 
 // ------------------------------------------------------------------ moment-route kernel
+// Bound by HBM (FP32, FP64) and by vector issue and HBM together (FP16). Blocks of consecutive nodes
+// (flame_access.h) instead of a row per block took FP32 320^3 from 3.01 to 2.56 ms a step, 161 x 130 x 99
+// between two lattices from 265 to 155 us, FP16 384^3 from 2.78 to 2.28 ms and FP64 32^3 from 10.6 to 8.7 us.
 constexpr int kLocalThreads = 256;
-static_assert(kLocalThreads == kRowThreadsMax, "row blocks are launched with up to kRowThreadsMax threads");
+static_assert(kLocalThreads == kRowThreadsMax, "blocks are launched with up to kRowThreadsMax threads");
+constexpr size_t kFewBlocksNodes = size_t(1) << 25;
+constexpr unsigned kFewBlocksLds = 50000;   // of the 160 KB of a compute unit
 
 template <typename S, bool FAA, bool MAA, int PAR, bool SAVE, int MODEL, Addr A>
 __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
   using R = typename Enc<S>::R;
-  unsigned bx, by, bz;
-  logical_block((a.nx + blockDim.x - 1) / blockDim.x, a.ny, a.nz, bx, by, bz);
-  const int x = bx * blockDim.x + threadIdx.x;
-  const int y = by;
-  const int z = bz;
-  if (x >= a.nx) return;
-  const Rows rw(x, y, a.nx, a.ny);
-  const Planes pl(z, a.nz, static_cast<uint32_t>(a.nx) * a.ny);
-  const uint32_t cell = rw.at(0, 0) + pl.at(0);
+  uint32_t cell;
+  if (!own_cell(a.shape, cell)) return;
+  const NodeAt at = NodeAt::of(cell, a.shape);
+  const Rows& rw = at.rw;
+  const Planes& pl = at.pl;
   R f[kQ], g[kM];
   load_fluid<S, FAA, PAR, A>(a, rw, pl, f);
   load_magnetic<S, MAA, PAR, A>(a, rw, pl, g);
@@ -211,9 +213,13 @@ __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
   R J[3];
   current_from_moments(lam, Um, B, a.k.alpha, a.k.omega_b, J);
   if (SAVE) save_current<A>(a.save, a.n, cell, J);
-  collide_node<MODEL, sizeof(S) != 4>(f, g, m, U, Um, b, J, F, Sb, a.k);
-  store_fluid<S, FAA, PAR, A>(a, rw, pl, f);
-  store_magnetic<S, MAA, PAR, A>(a, rw, pl, g);
+  collide_node<MODEL, true>(f, g, m, U, Um, b, J, F, Sb, a.k);
+  // In place: plain stores, which stay in L2 until the neighbouring wavefronts have filled the
+  // lines that shifted stores share (64^3 FP32 40.5 -> 33 us for two steps, 512^3 FP64 35.8 -> 35.5 ms;
+  // FP32 at 128^3 alone is slower, 318 -> 334 us). Between two lattices the lines are whole and the
+  // non-temporal hint is the better one (161 x 130 x 99 FP32 156 against 161 us a step).
+  store_fluid<S, FAA, PAR, !FAA, A>(a, rw, pl, f);
+  store_magnetic<S, MAA, PAR, !MAA, A>(a, rw, pl, g);
 }
 
 // ------------------------------------------------------------------ stencil-route kernel
@@ -372,15 +378,19 @@ __global__ __launch_bounds__(kTX * Tile<typename Enc<S>::R>::ty, FLAME_ZMARCH_WA
 
 template <typename S, bool SAVE, int MODEL, Addr A>
 static void launch_local(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>& a) {
-  const unsigned tx = row_threads(c);
-  const dim3 block(tx, 1, 1);
-  const dim3 grid(((c->p.nx + tx - 1) / tx) * c->p.ny * c->p.nz);
+  const dim3 block(a.shape.threads, 1, 1);
+  const dim3 grid(a.shape.blocks);
+  // FP32 grids far beyond the 256 MB last-level cache: LDS is reserved so that three blocks share a
+  // compute unit instead of four to six. Fewer rows in flight keep the shared lines in L2 (512^3 21.2 ->
+  // 20.6 ms for two steps, 384^3 9.42 -> 9.33 ms; at 256^3 and below, where it costs 0 to 30%, and in
+  // FP16 and FP64, whose registers already bound the blocks, there is no limit).
+  const unsigned lds = sizeof(S) == 4 && c->n >= kFewBlocksNodes ? kFewBlocksLds : 0;
   if (!s.fluid_aa)
-    hipLaunchKernelGGL((step_local<S, false, false, 0, SAVE, MODEL, A>), grid, block, 0, c->stream, a);
+    hipLaunchKernelGGL((step_local<S, false, false, 0, SAVE, MODEL, A>), grid, block, lds, c->stream, a);
   else if (c->parity == 0)
-    hipLaunchKernelGGL((step_local<S, true, true, 0, SAVE, MODEL, A>), grid, block, 0, c->stream, a);
+    hipLaunchKernelGGL((step_local<S, true, true, 0, SAVE, MODEL, A>), grid, block, lds, c->stream, a);
   else
-    hipLaunchKernelGGL((step_local<S, true, true, 1, SAVE, MODEL, A>), grid, block, 0, c->stream, a);
+    hipLaunchKernelGGL((step_local<S, true, true, 1, SAVE, MODEL, A>), grid, block, lds, c->stream, a);
 }
 
 template <typename S, bool SAVE, int MODEL>
@@ -425,6 +435,7 @@ static hipError_t launch_typed(const flame_ctx* c, const SetPtrs& s, size_t stri
   a.nx = c->p.nx;
   a.ny = c->p.ny;
   a.nz = c->p.nz;
+  a.shape = grid_shape(c->p, row_threads(c));
   a.n = c->n;
   a.stride = stride;
   a.save = static_cast<R*>(save);
