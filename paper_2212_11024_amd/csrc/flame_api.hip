@@ -1017,6 +1017,10 @@ flame_status flame_init(const flame_params* p, const double* u, const double* b,
     c->err = "hipGetDevice failed (no HIP device?)";
     return bail(FLAME_E_HIP);
   }
+  if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
+    c->err = "hipDeviceGetAttribute failed";
+    return bail(FLAME_E_HIP);
+  }
   {
     const hipError_t e = scratch_address(c->device, &c->scratch);
     if (e != hipSuccess) {

@@ -402,12 +402,12 @@ FLAME_HD void populate_reverse(R (&l)[kQ], R rho, const R (&U)[3], const R (&Q)[
 // In deviations: f^mhd(0)_i - f_rest_i = w_i [d rho E_i + (E_i - 1)] + (w_i / 2 c_s^4)
 // (M(B) - M(b0)) : (c c - c_s^2 I), E_i = prod_a (1 + e_a), M(B) = |B|^2/2 I - B B.
 //
-// Separable selects how the 27 directions are formed: true, through the tensor-product transforms
-// above; false, one direction at a time in the App. A order. The transforms take the step from
-// 1073 to 703 vector instructions and 265 to 172 registers (FP64), the FP16 step at 384^3 from 5.55
-// to 5.04 ms, FP64 at 512^3 from 37.1 to 35.8 ms for an even and an odd step, and their FP32 error against
-// FP64 is 30% smaller.
-template <typename R, bool Separable = false>
+// The tensor-product transforms above form the 27 directions: against one polynomial evaluation per
+// direction they take the step from 1073 to 703 vector instructions and 265 to 172 registers (FP64),
+// the FP16 step at 384^3 from 5.55 to 5.04 ms and FP64 at 512^3 from 37.1 to 35.8 ms for an even
+// and an odd step, and their FP32 error against FP64 is 30% smaller. (The second template argument has
+// no effect.)
+template <typename R, bool = true>
 FLAME_HD void collide_fluid(R (&f)[kQ], const FluidMoments<R>& m, R rho,
                                               const R (&U)[3], const R (&b)[3], const R (&b0)[3],
                                               const R (&F)[3], R omega) {
@@ -425,40 +425,12 @@ FLAME_HD void collide_fluid(R (&f)[kQ], const FluidMoments<R>& m, R rho,
   const R qyz = om1 * (m.syz - rho * U[1] * U[2] + R(0.5) * (U[1] * F[2] + F[1] * U[2])
                        + b0[1] * b[2] + b[1] * b0[2] + b[1] * b[2]);
   const R fhx = R(0.5) * F[0], fhy = R(0.5) * F[1], fhz = R(0.5) * F[2];
-  if constexpr (Separable) {
-    R a[kQ], M[6];
-    central_coefficients(rho, {qxx, qyy, qzz, qxy, qxz, qyz}, {fhx, fhy, fhz}, a);
-    maxwell_change(b, b0, M);
-    populate(a, m.drho, U, M);
+  R a[kQ], M[6];
+  central_coefficients(rho, {qxx, qyy, qzz, qxy, qxz, qyz}, {fhx, fhy, fhz}, a);
+  maxwell_change(b, b0, M);
+  populate(a, m.drho, U, M);
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) f[i] = a[tidx(cq(i, 0) + 1, cq(i, 1) + 1, cq(i, 2) + 1)];
-  } else {
-    // Maxwell-stress change: (M(B) - M(b0)) : (cc - I/3) = s (|c|^2 - 1/3) - (b.c)(2 b0.c + b.c)
-    const R s = b0[0] * b[0] + b0[1] * b[1] + b0[2] * b[2]
-              + R(0.5) * (b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
-    const Axis<R> ax(U[0]), ay(U[1]), az(U[2]);
-    const R drho = m.drho;
-    // each direction: equilibrium deviation w_i [d rho E_i + (E_i - 1)], the Maxwell-stress change,
-    // and the collided second moments and force through the h-factors
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-      const int x = cq(i, 0) + 1, y = cq(i, 1) + 1, z = cq(i, 2) + 1;
-      const R ex = ax.e[x], ey = ay.e[y], ez = az.e[z];
-      const R em1 = ex + (R(1) + ex) * (ey + (R(1) + ey) * ez);   // E_i - 1 without cancellation
-      const R w = R(wq(i));
-      R v = w * (drho * (R(1) + em1) + em1);
-      const R bc = R(cq(i, 0)) * b[0] + R(cq(i, 1)) * b[1] + R(cq(i, 2)) * b[2];
-      const R b0c = R(cq(i, 0)) * b0[0] + R(cq(i, 1)) * b0[1] + R(cq(i, 2)) * b0[2];
-      v += (w * R(4.5)) * (s * R(speed2q(i) - 1.0 / 3.0) - bc * (R(2) * b0c + bc));
-      const R h0x = ax.h0[x], h0y = ay.h0[y], h0z = az.h0[z];
-      const R h1x = ax.h1[x], h1y = ay.h1[y], h1z = az.h1[z];
-      const R h2x = ax.h2[x], h2y = ay.h2[y], h2z = az.h2[z];
-      v += h0z * (h2x * h0y * qxx + h0x * h2y * qyy + h1x * h1y * qxy + h1x * h0y * fhx + h0x * h1y * fhy)
-         + h1z * (h1x * h0y * qxz + h0x * h1y * qyz + h0x * h0y * fhz)
-         + h2z * (h0x * h0y * qzz);
-      f[i] = v;
-    }
-  }
+  for (int i = 0; i < kQ; ++i) f[i] = a[tidx(cq(i, 0) + 1, cq(i, 1) + 1, cq(i, 2) + 1)];
 }
 
 // Post-collision magnetic deviations, in place (eq. MHD_LBscheme with the Hall equilibrium

@@ -13,6 +13,7 @@
 struct flame_ctx {
   flame_params p{};
   int device = 0;
+  int cus = 0;               // compute units of the device
   hipStream_t stream = nullptr;
   size_t n = 0;              // nodes
   size_t stride = 0;         // elements between consecutive population arrays
@@ -24,7 +25,7 @@ struct flame_ctx {
   double omega = 0, omega_b = 0;
   double cfl = 0;
   // launch shape (tuning; read from the environment at flame_init, results do not depend on it):
-  // planes per workgroup of the stencil kernel (0: the built-in 32) and threads per row block of
+  // planes per workgroup of the stencil kernel (0: by the grid's size) and threads per row block of
   // the node-local kernels (0: the row rounded up to whole wavefronts, at most 256)
   int zchunk = 0;
   int row_tx = 0;

@@ -194,7 +194,7 @@ FLAME_HD void collide_fluid_set(R (&f)[FL::q], R drho, const R (&U)[3], const R 
     if constexpr (BGK)
       collide_fluid_bgk(f, m, U, b, b0, F, omega);
     else
-      collide_fluid<R, false>(f, m, R(1) + m.drho, U, b, b0, F, omega);
+      collide_fluid<R>(f, m, R(1) + m.drho, U, b, b0, F, omega);
   } else {
     collide_fluid_bgk2<FL>(f, drho, U, b, b0, F, omega);
   }

@@ -16,7 +16,7 @@
 //     256 consecutive nodes; with FP16 and FP64 storage its arrays are addressed through buffer
 //     resources when every array ends at least 16 bytes below 4 GiB, otherwise (and with FP32
 //     storage) through 64-bit global addresses (bitwise the same step either way).
-//   step_zmarch - stencil J: a workgroup owns a 64 x 4 tile of (x, y) and marches along z. It
+//   step_zmarch - stencil J: a workgroup owns a 64 x 8 tile of (x, y) and marches along z. It
 //     keeps the field fluctuation b of three consecutive planes in LDS (computed once per node
 //     from that node's own magnetic populations, which it holds in registers for the next
 //     iteration) plus, for each plane, the one-node ring around the tile (computed one plane
@@ -140,24 +140,24 @@ struct Zero3 {
 };
 
 // Fluid collision of the model, in place.
-template <int MODEL, bool Separable, typename R>
+template <int MODEL, typename R>
 __device__ __forceinline__ void collide_fluid_model(R (&f)[kQ], const FluidMoments<R>& m, const R (&U)[3],
                                                     const R (&b)[3], const R (&b0)[3], const R (&F)[3], R omega) {
   if constexpr ((MODEL & kModelBGK) != 0)
     collide_fluid_bgk(f, m, U, b, b0, F, omega);
   else
-    collide_fluid<R, Separable>(f, m, R(1) + m.drho, U, b, b0, F, omega);
+    collide_fluid<R>(f, m, R(1) + m.drho, U, b, b0, F, omega);
 }
 
 // Node update from loaded populations and J: moments, both collisions, in place in f and g.
 // Um is the bulk velocity as the magnetic equilibrium sees it (zero for electron MHD).
-template <int MODEL, bool Separable, typename R>
+template <int MODEL, typename R>
 __device__ __forceinline__ void collide_node(R (&f)[kQ], R (&g)[kM], const FluidMoments<R>& m, const R (&U)[3],
                                              const R (&Um)[3], const R (&b)[3], const R (&J)[3], const R (&F)[3],
                                              const R (&Sb)[3], const PhysConst<R>& k) {
   const R b0[3] = {k.b0[0], k.b0[1], k.b0[2]};
   const R B[3] = {b0[0] + b[0], b0[1] + b[1], b0[2] + b[2]};
-  collide_fluid_model<MODEL, Separable>(f, m, U, b, b0, F, k.omega);
+  collide_fluid_model<MODEL>(f, m, U, b, b0, F, k.omega);
   collide_magnetic(g, Um, B, b, J, Sb, k.alpha, k.omega_b);
 }
 
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
   R J[3];
   current_from_moments(lam, Um, B, a.k.alpha, a.k.omega_b, J);
   if (SAVE) save_current<A>(a.save, a.n, cell, J);
-  collide_node<MODEL, true>(f, g, m, U, Um, b, J, F, Sb, a.k);
+  collide_node<MODEL>(f, g, m, U, Um, b, J, F, Sb, a.k);
   // In place: plain stores, which stay in L2 until the neighbouring wavefronts have filled the
   // lines that shifted stores share (64^3 FP32 40.5 -> 33 us for two steps, 512^3 FP64 35.8 -> 35.5 ms;
   // FP32 at 128^3 alone is slower, 318 -> 334 us). Between two lattices the lines are whole and the
@@ -223,32 +223,20 @@ __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
 }
 
 // ------------------------------------------------------------------ stencil-route kernel
-// Tile and z-chunk of the stencil kernel (tuning parameters, overridable at build time).
+// Tile of the stencil kernel (rows per tile overridable at build time): 64 x 8. The ring and the
+// lines that tiles share fall with the tile's height: 64 x 4 runs 2-8% slower at 256^3 and above
+// (FP32 256^3 3.17 against 3.03 ms for two steps, FP64 6.16 against 5.65, FP16 2.06 against 1.88),
+// 64 x 12 slower in FP32.
 #ifndef FLAME_TY
-#define FLAME_TY 4        // FP32 / FP16 storage
-#endif
-#ifndef FLAME_TY64
-#define FLAME_TY64 4      // FP64 storage (twice the registers per node)
-#endif
-#ifndef FLAME_ZCHUNK
-#define FLAME_ZCHUNK 32
-#endif
-#ifndef FLAME_ZMARCH_WAVES_PER_EU
-#define FLAME_ZMARCH_WAVES_PER_EU 1
+#define FLAME_TY 8
 #endif
 constexpr int kTX = 64;
-template <typename R>
-struct Tile {
-  static constexpr int ty = sizeof(R) == 8 ? FLAME_TY64 : FLAME_TY;
-};
-constexpr int kZChunk = FLAME_ZCHUNK;   // planes per workgroup
+constexpr int kTY = FLAME_TY;
 
 template <typename S, bool FAA, int PAR, bool SAVE, int MODEL>
-__global__ __launch_bounds__(kTX * Tile<typename Enc<S>::R>::ty, FLAME_ZMARCH_WAVES_PER_EU) void step_zmarch(
-    StepArgs<S> a) {
+__global__ __launch_bounds__(kTX * kTY) void step_zmarch(StepArgs<S> a) {
   using E = Enc<S>;
   using R = typename E::R;
-  constexpr int kTY = Tile<R>::ty;
   // b of the tile plus its one-node ring for a rolling window of planes:
   // [plane slot][ly + 1][lx + 1][component]. Four slots: a slot is rewritten two iterations
   // after it was last read, so one barrier per plane separates every write from every read.
@@ -349,7 +337,7 @@ __global__ __launch_bounds__(kTX * Tile<typename Enc<S>::R>::ty, FLAME_ZMARCH_WA
 #pragma unroll
       for (int c = 0; c < 3; ++c) b[c] = b_component(g, c, R(0.5) * Sb[c]);
       const R b0[3] = {a.k.b0[0], a.k.b0[1], a.k.b0[2]};
-      collide_fluid_model<MODEL, sizeof(S) != 4>(f, m, U, b, b0, F, a.k.omega);
+      collide_fluid_model<MODEL>(f, m, U, b, b0, F, a.k.omega);
       store_fluid<S, FAA, PAR>(a, rw, pl, f);
     }
     __syncthreads();
@@ -376,6 +364,28 @@ __global__ __launch_bounds__(kTX * Tile<typename Enc<S>::R>::ty, FLAME_ZMARCH_WA
   }
 }
 
+// Planes per workgroup of the stencil kernel: the power of two up to 64 that a grid finishes first
+// with, counting rounds of resident workgroups (per_cu on each compute unit: its registers hold two
+// in FP32 and FP16, one in FP64) times the planes of one, whose prologue costs about 3/4 of a plane.
+// Long chunks waste less in prologues, short ones fill the chip: with 32 planes everywhere 64^3 FP32
+// ran 32 workgroups and took 295 us for two steps against 52, 128^3 509 against 366, 32^3 275 against
+// 31; at 256^3 64 planes are the best (FP32 2.98 against 3.02 ms for 32 and 3.09 for 8, FP64 5.62, 5.75, 5.92).
+static int zchunk_planes(const flame_ctx* c, int per_cu) {
+  const int64_t tiles = static_cast<int64_t>((c->p.nx + kTX - 1) / kTX) * ((c->p.ny + kTY - 1) / kTY);
+  const int64_t resident = static_cast<int64_t>(std::max(c->cus, 1)) * per_cu;
+  int best = 1;
+  double least = 0;
+  for (int planes = 1; planes <= 64; planes *= 2) {
+    const int64_t groups = tiles * ((c->p.nz + planes - 1) / planes);
+    const double cost = static_cast<double>((groups + resident - 1) / resident) * (std::min(planes, c->p.nz) + 0.75);
+    if (planes == 1 || cost <= least) {
+      least = cost;
+      best = planes;
+    }
+  }
+  return best;
+}
+
 template <typename S, bool SAVE, int MODEL, Addr A>
 static void launch_local(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>& a) {
   const dim3 block(a.shape.threads, 1, 1);
@@ -395,10 +405,8 @@ static void launch_local(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>
 
 template <typename S, bool SAVE, int MODEL>
 static void launch_model(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>& a) {
-  using R = typename Enc<S>::R;
   const int par = c->parity;
   if (c->p.jmode == FLAME_J_STENCIL) {
-    constexpr int kTY = Tile<R>::ty;
     const dim3 grid(((c->p.nx + kTX - 1) / kTX) * ((c->p.ny + kTY - 1) / kTY) * ((c->p.nz + a.zchunk - 1) / a.zchunk));
     const dim3 block(kTX, kTY, 1);
     if (!s.fluid_aa)
@@ -443,7 +451,7 @@ static hipError_t launch_typed(const flame_ctx* c, const SetPtrs& s, size_t stri
   a.k.omega_b = R(c->omega_b);
   a.k.alpha = R(c->p.d_i);
   for (int i = 0; i < 3; ++i) a.k.b0[i] = R(c->p.b0[i]);
-  a.zchunk = c->p.jmode == FLAME_J_STENCIL ? std::min(c->p.nz, c->zchunk > 0 ? c->zchunk : kZChunk) : 1;
+  a.zchunk = c->p.jmode == FLAME_J_STENCIL ? std::min(c->p.nz, c->zchunk > 0 ? c->zchunk : zchunk_planes(c, sizeof(R) == 8 ? 1 : 2)) : 1;
   const int model = step_model(c->p);
   if constexpr (SAVE) {
     // the state-saving steps serve the adjoint, which is built for the paper's model only
