@@ -24,41 +24,18 @@ struct AdjArgs {
   R* lam_j;            // [3][n] (stencil route)
   const R* force_u;
   const R* force_b;
-  int nx, ny, nz;
+  GridShape shape;
   size_t n;
   PhysConst<R> k;
 };
 
+// Bound by HBM: 100 loads and 48 stores per node. At least two waves per SIMD, which FP64 misses by a
+// few registers otherwise (48^3 20.5 -> 19.2 us). The adjoints of the fluid populations are folded into
+// 13 sums before the magnetic ones are needed, so neither kernel holds all 48 (FP32 115 registers).
+// FP32 128^3 252 -> 223 us, 200^3 1238 -> 904; FP64 128^3 645 -> 442, 48^3 42 -> 19.
 constexpr int kAdjThreads = 256;
-// Minimum waves per SIMD the reverse-pass kernels are compiled for (0: the compiler's choice).
-#ifndef FLAME_ADJ_WAVES_PER_EU
-#define FLAME_ADJ_WAVES_PER_EU 0
-#endif
-#if FLAME_ADJ_WAVES_PER_EU > 0
-#define FLAME_ADJ_BOUNDS __launch_bounds__(kAdjThreads, FLAME_ADJ_WAVES_PER_EU)
-#else
-#define FLAME_ADJ_BOUNDS __launch_bounds__(kAdjThreads)
-#endif
-
-// Keeps the scheduler from moving the gathers of the next step's adjoints above the forward
-// recomputation, so the pre-collision populations are dead before those values arrive (fewer
-// registers live at once). Off unless FLAME_ADJ_FENCE is set.
-#ifndef FLAME_ADJ_FENCE
-#define FLAME_ADJ_FENCE 0
-#endif
-__device__ __forceinline__ void adj_phase_fence() {
-  if (FLAME_ADJ_FENCE) __builtin_amdgcn_sched_barrier(0);
-}
-
-__device__ __forceinline__ size_t anode(int x, int y, int z, int nx, int ny) {
-  return (static_cast<size_t>(z) * ny + y) * nx + x;
-}
-
-// Addressing: 32-bit node offsets (Rows, Planes) from the uniform array bases, by 64-bit global
-// addresses. Buffer resources, which the forward step uses, raise these kernels' register count
-// to the 256 limit (one wave per SIMD) and slow the moment-route adjoint by 40%; the 32-bit
-// offsets alone took it from 0.257 to 0.245 ms per step at 128^3 FP32. The entry points refuse
-// arrays of more than 4 GiB.
+// Addressing: 32-bit node offsets from the uniform array bases, by 64-bit global addresses (buffer
+// resources run within 1% of them here). The entry points refuse arrays of more than 4 GiB.
 //
 // The adjoints of the next time level, gathered along the streaming: population q of node x went
 // to x + c_q, so its adjoint is lam_next[q] there.
@@ -106,16 +83,14 @@ __device__ __forceinline__ void reverse_node(const VjpState<R>& fw, const R (&F)
 }
 
 template <typename R, bool MOMENT>
-__global__ FLAME_ADJ_BOUNDS void adjoint_step_kernel(AdjArgs<R> a) {
+__global__ __launch_bounds__(kAdjThreads, 2) void adjoint_step_kernel(AdjArgs<R> a) {
   constexpr Addr A = Addr::Global;
-  unsigned bx, by, bz;
-  logical_block((a.nx + blockDim.x - 1) / blockDim.x, a.ny, a.nz, bx, by, bz);
-  const int x = bx * blockDim.x + threadIdx.x, y = by, z = bz;
-  if (x >= a.nx) return;
+  uint32_t cell;
+  if (!own_cell(a.shape, cell)) return;
   const size_t n = a.n;
-  const Rows rw(x, y, a.nx, a.ny);
-  const Planes pl(z, a.nz, static_cast<uint32_t>(a.nx) * a.ny);
-  const uint32_t cell = rw.at(0, 0) + pl.at(0);
+  const NodeAt at = NodeAt::of(cell, a.shape);
+  const Rows& rw = at.rw;
+  const Planes& pl = at.pl;
   R F[3];
   VjpState<R> fw;
   {
@@ -132,7 +107,6 @@ __global__ FLAME_ADJ_BOUNDS void adjoint_step_kernel(AdjArgs<R> a) {
     }
     fw = vjp_forward<R, MOMENT>(f, g, F, S, J, a.k);
   }
-  adj_phase_fence();
   reverse_node<A, R, MOMENT>(fw, F, a.k, a.lam_next, a.lam, a.lam_j, n, rw, pl, cell);
 }
 
@@ -145,24 +119,22 @@ struct AdjTraceArgs {
   R* lam;              // [48][n]
   const R* force_u;
   const R* force_b;
-  int nx, ny, nz;
+  GridShape shape;
   size_t n;
   PhysConst<R> k;
 };
 
 template <typename S>
-__global__ FLAME_ADJ_BOUNDS void adjoint_trace_kernel(AdjTraceArgs<S> a) {
+__global__ __launch_bounds__(kAdjThreads, 2) void adjoint_trace_kernel(AdjTraceArgs<S> a) {
   constexpr Addr A = Addr::Global;
   using E = Enc<S>;
   using R = typename E::R;
-  unsigned bx, by, bz;
-  logical_block((a.nx + blockDim.x - 1) / blockDim.x, a.ny, a.nz, bx, by, bz);
-  const int x = bx * blockDim.x + threadIdx.x, y = by, z = bz;
-  if (x >= a.nx) return;
+  uint32_t cell;
+  if (!own_cell(a.shape, cell)) return;
   const size_t n = a.n;
-  const Rows rw(x, y, a.nx, a.ny);
-  const Planes pl(z, a.nz, static_cast<uint32_t>(a.nx) * a.ny);
-  const uint32_t cell = rw.at(0, 0) + pl.at(0);
+  const NodeAt at = NodeAt::of(cell, a.shape);
+  const Rows& rw = at.rw;
+  const Planes& pl = at.pl;
   R F[3];
   VjpState<R> fw;
   {
@@ -188,22 +160,19 @@ __global__ FLAME_ADJ_BOUNDS void adjoint_trace_kernel(AdjTraceArgs<S> a) {
     const R unused[3] = {R(0), R(0), R(0)};
     fw = vjp_forward<R, true>(f, g, F, Sb, unused, a.k);
   }
-  adj_phase_fence();
   reverse_node<A, R, true>(fw, F, a.k, a.lam_next, a.lam, static_cast<R*>(nullptr), n, rw, pl, cell);
 }
 
 // Stencil route: b_c of every magnetic population set feeds J of the six face neighbours; add
 // curl(lam_J) (the transpose of the central-difference curl) to the adjoint of all 7 g_{i,c}.
 template <typename R>
-__global__ __launch_bounds__(kAdjThreads) void adjoint_curl_kernel(R* lam, const R* lam_j, int nx, int ny, int nz,
-                                                                    size_t n) {
-  unsigned bx, by, bz;
-  logical_block((nx + blockDim.x - 1) / blockDim.x, ny, nz, bx, by, bz);
-  const int x = bx * blockDim.x + threadIdx.x, y = by, z = bz;
-  if (x >= nx) return;
-  const size_t cell = anode(x, y, z, nx, ny);
+__global__ __launch_bounds__(kAdjThreads) void adjoint_curl_kernel(R* lam, const R* lam_j, GridShape shape, size_t n) {
+  constexpr Addr A = Addr::Global;
+  uint32_t cell;
+  if (!own_cell(shape, cell)) return;
+  const NodeAt at = NodeAt::of(cell, shape);
   auto L = [&](int c, int dx, int dy, int dz) {
-    return lam_j[static_cast<size_t>(c) * n + anode(wrap(x + dx, nx), wrap(y + dy, ny), wrap(z + dz, nz), nx, ny)];
+    return ld<A>(lam_j + static_cast<size_t>(c) * n, at.rw.at(dx, dy) + at.pl.at(dz));
   };
   const R cx = R(0.5) * (L(2, 0, 1, 0) - L(2, 0, -1, 0)) - R(0.5) * (L(1, 0, 0, 1) - L(1, 0, 0, -1));
   const R cy = R(0.5) * (L(0, 0, 0, 1) - L(0, 0, 0, -1)) - R(0.5) * (L(2, 1, 0, 0) - L(2, -1, 0, 0));
@@ -212,7 +181,10 @@ __global__ __launch_bounds__(kAdjThreads) void adjoint_curl_kernel(R* lam, const
 #pragma unroll
   for (int i = 0; i < 7; ++i)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) lam[static_cast<size_t>(kQ + i * 3 + c) * n + cell] += cc[c];
+    for (int c = 0; c < 3; ++c) {
+      R* base = lam + static_cast<size_t>(kQ + i * 3 + c) * n;
+      st<A, false>(base, cell, ld<A>(base, cell) + cc[c]);
+    }
 }
 
 // Adjoint of the initial state: d loss / d(u, b, grad u, grad b) from lam_0.
@@ -275,24 +247,20 @@ static hipError_t adjoint_typed(const flame_ctx* c, const void* state, const voi
   a.lam_j = static_cast<R*>(lam_j);
   a.force_u = static_cast<const R*>(c->p.force_u);
   a.force_b = static_cast<const R*>(c->p.force_b);
-  a.nx = c->p.nx;
-  a.ny = c->p.ny;
-  a.nz = c->p.nz;
+  a.shape = grid_shape(c->p, row_threads(c->p.nx));
   a.n = c->n;
   a.k.omega = R(c->omega);
   a.k.omega_b = R(c->omega_b);
   a.k.alpha = R(c->p.d_i);
   for (int i = 0; i < 3; ++i) a.k.b0[i] = R(c->p.b0[i]);
-  const unsigned tx = row_threads(c->p.nx);
-  const dim3 grid(((c->p.nx + tx - 1) / tx) * c->p.ny * c->p.nz);
+  const dim3 grid(a.shape.blocks), block(a.shape.threads);
   if (c->p.jmode == FLAME_J_STENCIL) {
-    hipLaunchKernelGGL((adjoint_step_kernel<R, false>), grid, dim3(tx), 0, c->stream, a);
+    hipLaunchKernelGGL((adjoint_step_kernel<R, false>), grid, block, 0, c->stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(adjoint_curl_kernel<R>, grid, dim3(tx), 0, c->stream, a.lam, a.lam_j, a.nx, a.ny,
-                       a.nz, a.n);
+    hipLaunchKernelGGL(adjoint_curl_kernel<R>, grid, block, 0, c->stream, a.lam, a.lam_j, a.shape, a.n);
   } else {
-    hipLaunchKernelGGL((adjoint_step_kernel<R, true>), grid, dim3(tx), 0, c->stream, a);
+    hipLaunchKernelGGL((adjoint_step_kernel<R, true>), grid, block, 0, c->stream, a);
   }
   return hipGetLastError();
 }
@@ -306,17 +274,14 @@ static hipError_t adjoint_trace_typed(const flame_ctx* c, const void* src, const
   a.lam = static_cast<R*>(lam);
   a.force_u = static_cast<const R*>(c->p.force_u);
   a.force_b = static_cast<const R*>(c->p.force_b);
-  a.nx = c->p.nx;
-  a.ny = c->p.ny;
-  a.nz = c->p.nz;
+  a.shape = grid_shape(c->p, row_threads(c->p.nx));
   a.n = c->n;
   a.k.omega = R(c->omega);
   a.k.omega_b = R(c->omega_b);
   a.k.alpha = R(c->p.d_i);
   for (int i = 0; i < 3; ++i) a.k.b0[i] = R(c->p.b0[i]);
-  const unsigned tx = row_threads(a.nx);
-  const dim3 grid(((a.nx + tx - 1) / tx) * a.ny * a.nz);
-  hipLaunchKernelGGL(adjoint_trace_kernel<S>, grid, dim3(tx), 0, c->stream, a);
+  const dim3 grid(a.shape.blocks), block(a.shape.threads);
+  hipLaunchKernelGGL(adjoint_trace_kernel<S>, grid, block, 0, c->stream, a);
   return hipGetLastError();
 }
 

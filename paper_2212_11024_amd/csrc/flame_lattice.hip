@@ -4,7 +4,7 @@
 // (flame_step.hip, flame_api.hip); this file serves every other pair, with the same storage
 // encodings, layouts (AA in place for both sets, or two lattices with pull streaming), canonical
 // ordering rules and FP64 diagnostics:
-//   - a node-local fused step (one node per thread, rows of up to 256 nodes per block);
+//   - a node-local fused step (one node per thread, blocks of up to 256 consecutive nodes);
 //   - the initial state, canonical copies, node fields, reduction partials and the field
 //     components the spectra transform.
 // Readings the paper leaves open (velocity orders, magnetic weights, the D3Q19 equilibrium and
@@ -12,6 +12,7 @@
 
 #include <math.h>
 
+#include "flame_access.h"
 #include "flame_internal.h"
 #include "flame_lattice.h"
 
@@ -56,64 +57,59 @@ struct VStepArgs {
   S* g_dst;
   const R* force_u;
   const R* force_b;
-  int nx, ny, nz;
+  GridShape shape;
   size_t n, stride;
   PhysConst<R> k;
 };
 
-// AA: both sets in place (PAR: even 0 / odd 1); else two-lattice pull for both.
+// AA: both sets in place (PAR: even 0 / odd 1); else two-lattice pull for both. Bound by HBM; blocks of
+// consecutive nodes and store hints as in the paper pair's kernel (flame_access.h, flame_step.hip).
 template <typename S, typename FL, typename ML, bool AA, int PAR, bool BGK, bool EMHD>
-__global__ __launch_bounds__(256) void variant_step(VStepArgs<S> a) {
+__global__ __launch_bounds__(kRowThreadsMax) void variant_step(VStepArgs<S> a) {
   using E = Enc<S>;
   using R = typename E::R;
+  constexpr Addr A = Addr::Global;
   constexpr int Q = FL::q, NG = ML::m * 3;
-  unsigned bx, by, bz;
-  logical_block((a.nx + blockDim.x - 1) / blockDim.x, a.ny, a.nz, bx, by, bz);
-  const int x = bx * blockDim.x + threadIdx.x, y = by, z = bz;
-  if (x >= a.nx) return;
-  const int nx = a.nx, ny = a.ny, nz = a.nz;
-  const size_t cell = vnode(x, y, z, nx, ny);
-  const SetGeom geo{nx, ny, nz, a.stride};
-  const int rmode = AA ? PAR : 2;
+  constexpr bool own = AA && PAR == 0;   // reads and writes at the node itself
+  uint32_t cell;
+  if (!own_cell(a.shape, cell)) return;
+  const NodeAt at = NodeAt::of(cell, a.shape);
   R f[Q], g[NG];
 #pragma unroll
-  for (int i = 0; i < Q; ++i)
-    f[i] = E::dec(a.f_src[geo.at(rmode, i, FL::opp(i), FL::c(i, 0), FL::c(i, 1), FL::c(i, 2), x, y, z)],
-                  R(1.0 / fscale<S, FL>(i)));
+  for (int i = 0; i < Q; ++i) {
+    const uint32_t off = own ? cell : at.rw.at(-FL::c(i, 0), -FL::c(i, 1)) + at.pl.at(-FL::c(i, 2));
+    const S* base = a.f_src + static_cast<size_t>(AA && PAR == 1 ? FL::opp(i) : i) * a.stride;
+    f[i] = E::dec(ld<A>(base, off), R(1.0 / fscale<S, FL>(i)));
+  }
 #pragma unroll
   for (int i = 0; i < ML::m; ++i) {
-    const size_t slot = geo.slot(rmode, i, ML::opp(i));
-    const size_t node = geo.node(rmode, ML::xi(i, 0), ML::xi(i, 1), ML::xi(i, 2), x, y, z);
+    const uint32_t off = own ? cell : at.rw.at(-ML::xi(i, 0), -ML::xi(i, 1)) + at.pl.at(-ML::xi(i, 2));
+    const size_t slot = AA && PAR == 1 ? ML::opp(i) : i;
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      g[i * 3 + c] = E::dec(a.g_src[(slot * 3 + c) * a.stride + node], R(1.0 / fscale<S, ML>(i)));
+      g[i * 3 + c] = E::dec(ld<A>(a.g_src + (slot * 3 + c) * a.stride, off), R(1.0 / fscale<S, ML>(i)));
   }
   R F[3], Sb[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    F[c] = a.force_u ? a.force_u[static_cast<size_t>(c) * a.n + cell] : R(0);
-    Sb[c] = a.force_b ? a.force_b[static_cast<size_t>(c) * a.n + cell] : R(0);
+    F[c] = a.force_u ? ld<A>(a.force_u + static_cast<size_t>(c) * a.n, cell) : R(0);
+    Sb[c] = a.force_b ? ld<A>(a.force_b + static_cast<size_t>(c) * a.n, cell) : R(0);
   }
   variant_node<FL, ML, BGK, EMHD>(f, g, F, Sb, a.k);
   // stores: AA even: slot opp(i) at x; AA odd: slot i at x + v; pull: slot i at x (other copy)
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    size_t idx;
-    if (AA && PAR == 0) idx = static_cast<size_t>(FL::opp(i)) * a.stride + cell;
-    else if (AA) idx = static_cast<size_t>(i) * a.stride + vnode(wrap(x + FL::c(i, 0), nx), wrap(y + FL::c(i, 1), ny),
-                                                             wrap(z + FL::c(i, 2), nz), nx, ny);
-    else idx = static_cast<size_t>(i) * a.stride + cell;
-    a.f_dst[idx] = E::enc(f[i], R(fscale<S, FL>(i)));
+    const uint32_t off = AA && PAR == 1 ? at.rw.at(FL::c(i, 0), FL::c(i, 1)) + at.pl.at(FL::c(i, 2)) : cell;
+    S* base = a.f_dst + static_cast<size_t>(own ? FL::opp(i) : i) * a.stride;
+    st<A, !AA>(base, off, E::enc(f[i], R(fscale<S, FL>(i))));
   }
 #pragma unroll
   for (int i = 0; i < ML::m; ++i) {
-    size_t slot, node;
-    if (AA && PAR == 0) { slot = ML::opp(i); node = cell; }
-    else if (AA) { slot = i; node = vnode(wrap(x + ML::xi(i, 0), nx), wrap(y + ML::xi(i, 1), ny), wrap(z + ML::xi(i, 2), nz), nx, ny); }
-    else { slot = i; node = cell; }
+    const uint32_t off = AA && PAR == 1 ? at.rw.at(ML::xi(i, 0), ML::xi(i, 1)) + at.pl.at(ML::xi(i, 2)) : cell;
+    const size_t slot = own ? ML::opp(i) : i;
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      a.g_dst[(slot * 3 + c) * a.stride + node] = E::enc(g[i * 3 + c], R(fscale<S, ML>(i)));
+      st<A, !AA>(a.g_dst + (slot * 3 + c) * a.stride, off, E::enc(g[i * 3 + c], R(fscale<S, ML>(i))));
   }
 }
 
@@ -532,25 +528,22 @@ hipError_t variant_launch_step(const flame_ctx* c, const SetPtrs& s) {
     a.g_dst = static_cast<S*>(s.g_dst);
     a.force_u = static_cast<const R*>(c->p.force_u);
     a.force_b = static_cast<const R*>(c->p.force_b);
-    a.nx = c->p.nx;
-    a.ny = c->p.ny;
-    a.nz = c->p.nz;
+    a.shape = grid_shape(c->p, row_threads(c));
     a.n = c->n;
     a.stride = c->stride;
     a.k.omega = R(c->omega);
     a.k.omega_b = R(c->omega_b);
     a.k.alpha = R(c->p.d_i);
     for (int i = 0; i < 3; ++i) a.k.b0[i] = R(c->p.b0[i]);
-    const unsigned tx = row_threads(c);
-    const dim3 grid(((c->p.nx + tx - 1) / tx) * c->p.ny * c->p.nz);
+    const dim3 grid(a.shape.blocks), block(a.shape.threads);
     const bool bgk = c->p.collision == FLAME_COLLISION_BGK, emhd = c->p.magnetic == FLAME_MAGNETIC_EMHD;
     auto go = [&](auto aa, auto par) {
       constexpr bool AA = decltype(aa)::value;
       constexpr int PAR = decltype(par)::value;
-      if (bgk && emhd) hipLaunchKernelGGL((variant_step<S, FL, ML, AA, PAR, true, true>), grid, dim3(tx), 0, c->stream, a);
-      else if (bgk) hipLaunchKernelGGL((variant_step<S, FL, ML, AA, PAR, true, false>), grid, dim3(tx), 0, c->stream, a);
-      else if (emhd) hipLaunchKernelGGL((variant_step<S, FL, ML, AA, PAR, false, true>), grid, dim3(tx), 0, c->stream, a);
-      else hipLaunchKernelGGL((variant_step<S, FL, ML, AA, PAR, false, false>), grid, dim3(tx), 0, c->stream, a);
+      if (bgk && emhd) hipLaunchKernelGGL((variant_step<S, FL, ML, AA, PAR, true, true>), grid, block, 0, c->stream, a);
+      else if (bgk) hipLaunchKernelGGL((variant_step<S, FL, ML, AA, PAR, true, false>), grid, block, 0, c->stream, a);
+      else if (emhd) hipLaunchKernelGGL((variant_step<S, FL, ML, AA, PAR, false, true>), grid, block, 0, c->stream, a);
+      else hipLaunchKernelGGL((variant_step<S, FL, ML, AA, PAR, false, false>), grid, block, 0, c->stream, a);
     };
     if (!s.fluid_aa) go(std::false_type{}, std::integral_constant<int, 0>{});
     else if (c->parity == 0) go(std::true_type{}, std::integral_constant<int, 0>{});

@@ -217,9 +217,10 @@ __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
   // In place: plain stores, which stay in L2 until the neighbouring wavefronts have filled the
   // lines that shifted stores share (64^3 FP32 40.5 -> 33 us for two steps, 512^3 FP64 35.8 -> 35.5 ms;
   // FP32 at 128^3 alone is slower, 318 -> 334 us). Between two lattices the lines are whole and the
-  // non-temporal hint is the better one (161 x 130 x 99 FP32 156 against 161 us a step).
-  store_fluid<S, FAA, PAR, !FAA, A>(a, rw, pl, f);
-  store_magnetic<S, MAA, PAR, !MAA, A>(a, rw, pl, g);
+  // non-temporal hint is the better one (161 x 130 x 99 FP32 156 against 161 us a step), as it is
+  // beside a state that is written out (128^3 FP32).
+  store_fluid<S, FAA, PAR, !FAA || SAVE, A>(a, rw, pl, f);
+  store_magnetic<S, MAA, PAR, !MAA || SAVE, A>(a, rw, pl, g);
 }
 
 // ------------------------------------------------------------------ stencil-route kernel
