@@ -11,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "flame_access.h"
 #include "flame_internal.h"
 
 namespace flame {
@@ -484,18 +485,30 @@ __global__ __launch_bounds__(kRedThreads, 2) void reduce_kernel(AuxArgs<S> a, do
   if (threadIdx.x < FLAME_NRED) partials[blockIdx.x * FLAME_NRED + threadIdx.x] = sh[threadIdx.x][0];
 }
 
-// Fixed-order merge of the block partials of reduce_kernel into the FLAME_NRED results: thread k
-// runs over the blocks in order for slot k (sums; maxima for slots 4 and 6) and normalises the
-// slot as flame_reduce documents (node averages, rms, plain sums and maxima).
-__global__ __launch_bounds__(64) void reduce_merge_kernel(const double* partials, int blocks, double n,
-                                                          double* out) {
-  const int k = threadIdx.x;
-  if (k >= FLAME_NRED) return;
+// Fixed-order merge of the block partials of reduce_kernel into the FLAME_NRED results: thread
+// (g, k) runs over the blocks g, g + 64, ... in order for slot k (sums; maxima for slots 4 and 6), the
+// 64 groups meet in a fixed tree, and the slot is normalised as flame_reduce documents (node
+// averages, rms, plain sums and maxima). One thread per slot over all 2048 blocks took 700 us, as
+// long as the reduction of 200^3 nodes; this takes 7.
+constexpr int kMergeGroups = 64;
+__global__ __launch_bounds__(kMergeGroups * FLAME_NRED) void reduce_merge_kernel(const double* partials, int blocks,
+                                                                                 double n, double* out) {
+  __shared__ double sh[kMergeGroups][FLAME_NRED];
+  const int k = threadIdx.x % FLAME_NRED, g = threadIdx.x / FLAME_NRED;
+  const bool max_slot = k == 4 || k == 6;
   double acc = 0.0;
-  for (int b = 0; b < blocks; ++b) {
+  for (int b = g; b < blocks; b += kMergeGroups) {
     const double v = partials[static_cast<size_t>(b) * FLAME_NRED + k];
-    acc = (k == 4 || k == 6) ? fmax(acc, v) : acc + v;
+    acc = max_slot ? fmax(acc, v) : acc + v;
   }
+  sh[g][k] = acc;
+  __syncthreads();
+  for (int s = kMergeGroups / 2; s > 0; s >>= 1) {
+    if (g < s) sh[g][k] = max_slot ? fmax(sh[g][k], sh[g + s][k]) : sh[g][k] + sh[g + s][k];
+    __syncthreads();
+  }
+  if (g > 0) return;
+  acc = sh[0][k];
   if (k <= 3) acc = acc / n;
   else if (k == 5 || k == 7) acc = sqrt(acc / n);
   out[k] = acc;
@@ -512,114 +525,170 @@ static __device__ __align__(256) double scratch[flame::kRedBlocksMax * FLAME_NRE
 namespace flame {
 
 // ------------------------------------------------------------------ spectra
+// Real fields that are transformed in place lie in rows of 2 (nx / 2 + 1) values, component arrays
+// one after another.
+__device__ __forceinline__ size_t padded_index(uint32_t cell, const GridShape& g, uint32_t pitch) {
+  uint32_t x;
+  const uint32_t row = div_by(cell, g.nx, x);
+  return static_cast<size_t>(row) * pitch + x;
+}
+
+// Components first .. first + count - 1 of u (field 0) or B (field 1), each at dist doubles from
+// the one before. The node's populations are read once for all of them.
 template <typename S>
-__global__ __launch_bounds__(256) void field_component_kernel(AuxArgs<S> a, int field, int comp, double* out) {
-  const size_t cell = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void field_kernel(AuxArgs<S> a, GridShape shape, int field, int first, int count,
+                                                    uint32_t pitch, size_t dist, double* out) {
+  const size_t cell = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
   if (cell >= a.v.n) return;
   int x, y, z;
   node_xyz(cell, a.v.nx, a.v.ny, x, y, z);
   const View<S>& v = a.v;
+  double r[3];
   if (field == 0) {
-    double drho = 0, j = 0;
+    double f[kQ];
+    if (v.fmode == 0) view_fluid<0>(v, x, y, z, f);
+    else if (v.fmode == 1) view_fluid<1>(v, x, y, z, f);
+    else view_fluid<2>(v, x, y, z, f);
+    double drho = 0, j[3] = {0, 0, 0};
+#pragma unroll
     for (int i = 0; i < kQ; ++i) {
-      const double fi = v.f(i, x, y, z);
-      drho += fi;
-      j += cq(i, comp) * fi;
+      drho += f[i];
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (cq(i, c) != 0) j[c] += cq(i, c) * f[i];
     }
-    const double F = a.force_u ? static_cast<double>(a.force_u[comp * v.n + cell]) : 0.0;
-    out[cell] = (j + 0.5 * F) / (1.0 + drho);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const double F = a.force_u ? static_cast<double>(a.force_u[static_cast<size_t>(c) * v.n + cell]) : 0.0;
+      r[c] = (j[c] + 0.5 * F) / (1.0 + drho);
+    }
   } else {
-    out[cell] = a.b0[comp] + field_fluct(a, comp, x, y, z);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      r[c] = a.b0[c] + (v.gmode == 0   ? field_fluct_m<0>(a, c, x, y, z)
+                        : v.gmode == 1 ? field_fluct_m<1>(a, c, x, y, z)
+                                       : field_fluct_m<2>(a, c, x, y, z));
   }
+  double* at = out + padded_index(static_cast<uint32_t>(cell), shape, pitch);
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    if (c >= first && c < first + count) at[static_cast<size_t>(c - first) * dist] = r[c];
 }
 
 constexpr int kSpecShellsMax = 4096;
 
 __device__ __forceinline__ int signed_freq(int idx, int n) { return idx <= (n - 1) / 2 ? idx : idx - n; }
 
-// Shell binning without atomics. A binning block is one wavefront; it visits its entries in the
-// fixed order of a grid-stride loop, 64 at a time, and adds each group's contributions shell by
-// shell: the lanes holding one shell are summed by a fixed tree across the wavefront (the other
-// lanes contribute +0), and lane 0 adds that sum to the block's LDS bins, which only it writes.
-// The block partials are then merged in block order (bin_merge_kernel). Every sum therefore has
-// one fixed order for a given grid, and spectra are bitwise reproducible.
+// Shell binning without atomics. A binning block is one wavefront; it visits pieces of 64
+// consecutive k_x of one (k_y, k_z) row in the fixed order of a grid-stride loop. Along such a piece
+// the shell never decreases, so the entries of one shell are neighbouring lanes: a segmented scan in
+// a fixed tree leaves each shell's sum in its last lane, which adds it to the block's LDS bins (one
+// lane per shell). The block partials are then merged in a fixed order (bin_merge_kernel). Every
+// sum therefore has one order for a given grid, and spectra are bitwise reproducible. All components
+// are summed at an entry before it is binned. (A pass over the shells present among the lanes, with a
+// sum over the wavefront for each, took 472 us per component at 256^3; this takes 100 for three.)
 constexpr int kBinThreads = 64;
-constexpr int kBinBlocksMax = 2048;
+constexpr int kBinBlocksMax = 4096;
 
-// Lane 0 receives the sum of x over the 64 lanes, in a fixed tree order.
-__device__ __forceinline__ double wave_sum_fixed(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, kBinThreads);
-  return x;
+// Pieces of a half spectrum of rows of nxh entries.
+struct HalfShape {
+  int nx, ny, nz, nxh;
+  uint32_t pieces;        // per row
+  uint32_t total;         // pieces over all rows: at most 2^31, the nodes of the largest grid
+  size_t nh;              // entries
+};
+
+// The entry of this lane in piece t: its index, or none (shell -1) beyond the row's end.
+struct BinEntry {
+  size_t k;
+  int kx, ky, kz, shell;
+};
+__device__ __forceinline__ BinEntry bin_entry(uint32_t t, const HalfShape& h) {
+  const uint32_t row = t / h.pieces, piece = t - row * h.pieces;
+  BinEntry e;
+  e.kz = static_cast<int>(row / static_cast<uint32_t>(h.ny));
+  e.ky = static_cast<int>(row) - e.kz * h.ny;
+  e.kx = static_cast<int>(piece * kBinThreads + threadIdx.x);
+  e.k = static_cast<size_t>(row) * h.nxh + e.kx;
+  const double fx = e.kx, fy = signed_freq(e.ky, h.ny), fz = signed_freq(e.kz, h.nz);
+  e.shell = e.kx < h.nxh ? static_cast<int>(floor(sqrt(fx * fx + fy * fy + fz * fz) + 0.5)) : -1;
+  return e;
 }
 
-// Add v to bins[shell] for every lane (shell < 0: nothing). Called by all 64 lanes together.
-__device__ __forceinline__ void bin_group(double* bins, int shell, double v) {
-  unsigned long long pending = __ballot(shell >= 0);
-  while (pending) {
-    const int leader = __ffsll(static_cast<long long>(pending)) - 1;
-    const int s = __shfl(shell, leader, kBinThreads);
-    const bool mine = shell == s;
-    const double sum = wave_sum_fixed(mine ? v : 0.0);
-    if (threadIdx.x == 0) bins[s] += sum;
-    pending &= ~__ballot(mine);
+// Add v of every lane to bins[shell]; called by all 64 lanes together.
+__device__ __forceinline__ void bin_piece(double* bins, int nshells, int shell, double v) {
+  const int lane = threadIdx.x;
+#pragma unroll
+  for (int off = 1; off < kBinThreads; off <<= 1) {
+    const double below = __shfl_up(v, off, kBinThreads);
+    const int s = __shfl_up(shell, off, kBinThreads);
+    if (lane >= off && s == shell) v += below;
+  }
+  const int next = __shfl_down(shell, 1, kBinThreads);
+  if ((lane == kBinThreads - 1 || next != shell) && shell >= 0 && shell < nshells) bins[shell] += v;
+}
+
+// Block partials of the bins, one row of nshells per block; added to what is there unless first.
+__device__ __forceinline__ void bins_out(const double* bins, int nshells, int first, double* partials) {
+  for (int s = threadIdx.x; s < nshells; s += kBinThreads) {
+    double& out = partials[static_cast<size_t>(blockIdx.x) * nshells + s];
+    out = first ? bins[s] : out + bins[s];
   }
 }
 
-// Half-spectrum (nz, ny, nx/2+1) of an r2c transform; each entry stands for itself and, for
-// 0 < kx < nx - kx, its conjugate mirror at -k (same shell). Each entry adds w |X|^2 norm2 to
+// Half-spectra (nz, ny, nx/2+1) of r2c transforms, comps of them; each entry stands for itself and,
+// for 0 < kx < nx - kx, its conjugate mirror at -k (same shell). Each entry adds w |X|^2 norm2 to
 // its shell: w = 1/2 for the energy spectrum; w = |q|^2, q_a = 2 pi k_a / n_a, for the
-// dissipation spectrum (k2 set). Block partials [gridDim.x][nshells].
-__global__ __launch_bounds__(kBinThreads) void shell_bin_kernel(const hipfftDoubleComplex* X, int nx, int ny,
-                                                                int nz, int nshells, double norm2, int k2,
+// dissipation spectrum (k2 set).
+__global__ __launch_bounds__(kBinThreads) void shell_bin_kernel(const hipfftDoubleComplex* X, int comps, HalfShape h,
+                                                                int nshells, double norm2, int k2, int first,
                                                                 double* partials) {
   extern __shared__ double bins[];
-  for (int s = threadIdx.x; s < nshells; s += blockDim.x) bins[s] = 0.0;
-  __syncthreads();
-  const int nxh = nx / 2 + 1;
-  const size_t total = static_cast<size_t>(nz) * ny * nxh;
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  // the loop bound is uniform over the wavefront, so every lane takes part in every group
-  for (size_t base = static_cast<size_t>(blockIdx.x) * blockDim.x; base < total; base += stride) {
-    const size_t k = base + threadIdx.x;
-    int shell = -1;
+  for (int s = threadIdx.x; s < nshells; s += kBinThreads) bins[s] = 0.0;
+  for (uint32_t t = blockIdx.x; t < h.total; t += gridDim.x) {
+    const BinEntry e = bin_entry(t, h);
     double v = 0.0;
-    if (k < total) {
-      const int kx = static_cast<int>(k % nxh);
-      const size_t r = k / nxh;
-      const int ky = static_cast<int>(r % ny);
-      const int kz = static_cast<int>(r / ny);
-      const double fx = kx, fy = signed_freq(ky, ny), fz = signed_freq(kz, nz);
-      shell = static_cast<int>(floor(sqrt(fx * fx + fy * fy + fz * fz) + 0.5));
-      if (shell < nshells) {
-        const double re = X[k].x, im = X[k].y;
-        const double mult = (kx == 0 || 2 * kx == nx) ? 1.0 : 2.0;
-        double w = 0.5;
-        if (k2) {
-          const double qx = (2.0 * M_PI / nx) * fx, qy = (2.0 * M_PI / ny) * fy, qz = (2.0 * M_PI / nz) * fz;
-          w = qx * qx + qy * qy + qz * qz;
-        }
-        v = mult * w * (re * re + im * im) * norm2;
-      } else {
-        shell = -1;
+    if (e.shell >= 0 && e.shell < nshells) {
+      double p = 0.0;
+      for (int c = 0; c < comps; ++c) {
+        const hipfftDoubleComplex x = X[c * h.nh + e.k];
+        p += x.x * x.x + x.y * x.y;
       }
+      double w = 0.5;
+      if (k2) {
+        const double qx = (2.0 * M_PI / h.nx) * e.kx, qy = (2.0 * M_PI / h.ny) * signed_freq(e.ky, h.ny),
+                     qz = (2.0 * M_PI / h.nz) * signed_freq(e.kz, h.nz);
+        w = qx * qx + qy * qy + qz * qz;
+      }
+      v = ((e.kx == 0 || 2 * e.kx == h.nx) ? 1.0 : 2.0) * w * p * norm2;
     }
-    bin_group(bins, shell, v);
+    bin_piece(bins, nshells, e.shell, v);
   }
-  __syncthreads();
-  for (int s = threadIdx.x; s < nshells; s += blockDim.x) partials[static_cast<size_t>(blockIdx.x) * nshells + s] = bins[s];
+  bins_out(bins, nshells, first, partials);
 }
 
-// out[t][s] = sum over blocks, in block order, of partials[t][block][s] (terms t < gridDim.y).
-__global__ __launch_bounds__(256) void bin_merge_kernel(const double* partials, int blocks, int nshells,
-                                                        double* out) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nshells) return;
+// out[t][s] = sum over blocks of partials[t][block][s] (terms t < gridDim.y): thread (g, s) runs
+// over the blocks g, g + 16, ... in order, the 16 groups meet in a fixed tree.
+constexpr int kBinMergeShells = 16;
+constexpr int kBinMergeGroups = 16;
+__global__ __launch_bounds__(kBinMergeShells * kBinMergeGroups) void bin_merge_kernel(const double* partials, int blocks,
+                                                                                      int nshells, double* out) {
+  __shared__ double sh[kBinMergeGroups][kBinMergeShells];
+  const int l = threadIdx.x % kBinMergeShells, g = threadIdx.x / kBinMergeShells;
+  const int s = blockIdx.x * kBinMergeShells + l;
   const size_t t = blockIdx.y;
-  const double* p = partials + t * blocks * nshells + s;
   double acc = 0.0;
-  for (int b = 0; b < blocks; ++b) acc += p[static_cast<size_t>(b) * nshells];
-  out[t * nshells + s] = acc;
+  if (s < nshells) {
+    const double* p = partials + t * blocks * nshells + s;
+    for (int b = g; b < blocks; b += kBinMergeGroups) acc += p[static_cast<size_t>(b) * nshells];
+  }
+  sh[g][l] = acc;
+  __syncthreads();
+  for (int w = kBinMergeGroups / 2; w > 0; w >>= 1) {
+    if (g < w) sh[g][l] += sh[g + w][l];
+    __syncthreads();
+  }
+  if (g == 0 && s < nshells) out[t * nshells + s] = sh[0][l];
 }
 
 // ------------------------------------------------------------------ energy transfer
@@ -629,99 +698,109 @@ __device__ __forceinline__ double deriv_q(int idx, int n) {
   return 2 * idx == n ? 0.0 : (2.0 * M_PI / n) * signed_freq(idx, n);
 }
 
-__device__ __forceinline__ void half_index(size_t k, int nx, int ny, int& kx, int& ky, int& kz) {
-  const int nxh = nx / 2 + 1;
-  kx = static_cast<int>(k % nxh);
-  const size_t r = k / nxh;
-  ky = static_cast<int>(r % ny);
-  kz = static_cast<int>(r / ny);
+// Padded copies (rows of pitch values, dist apart) of three arrays of n nodes each: what the
+// in-place transforms read.
+__global__ __launch_bounds__(256) void pad_kernel(const double* src, GridShape g, uint32_t pitch, size_t dist, double* dst) {
+  const uint32_t cell = blockIdx.x * 256u + threadIdx.x;
+  if (cell >= g.n) return;
+  double* at = dst + padded_index(cell, g, pitch);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) at[c * dist] = src[static_cast<size_t>(c) * g.n + cell];
 }
 
-// out = i q_axis X / ncell on the half spectrum: the inverse real transform of out is the
-// derivative along axis of the field whose unnormalised forward transform is X.
-__global__ __launch_bounds__(256) void spectral_derivative_kernel(const hipfftDoubleComplex* X, int nx, int ny,
-                                                                  int nz, int axis, double inv_n,
+// out_a = i q_a X / ncell on the half spectrum for the axes first .. first + count - 1: the inverse
+// real transform of out_a is the derivative along a of the field whose unnormalised forward
+// transform is X.
+__global__ __launch_bounds__(256) void spectral_derivative_kernel(const hipfftDoubleComplex* X, HalfShape h, Divisor row,
+                                                                  Divisor rows, double inv_n, int first, int count,
                                                                   hipfftDoubleComplex* out) {
-  const size_t total = static_cast<size_t>(nz) * ny * (nx / 2 + 1);
-  const size_t k = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (k >= total) return;
-  int kx, ky, kz;
-  half_index(k, nx, ny, kx, ky, kz);
-  const double q = (axis == 0 ? deriv_q(kx, nx) : axis == 1 ? deriv_q(ky, ny) : deriv_q(kz, nz)) * inv_n;
+  const size_t k = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (k >= h.nh) return;
+  uint32_t kx, ky;
+  const uint32_t r = div_by(static_cast<uint32_t>(k), row, kx);
+  const uint32_t kz = div_by(r, rows, ky);
+  const double q[3] = {deriv_q(kx, h.nx) * inv_n, deriv_q(ky, h.ny) * inv_n, deriv_q(kz, h.nz) * inv_n};
   const hipfftDoubleComplex x = X[k];
-  out[k] = make_hipDoubleComplex(-q * x.y, q * x.x);
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    if (a >= first && a < first + count) out[(a - first) * h.nh + k] = make_hipDoubleComplex(-q[a] * x.y, q[a] * x.x);
 }
 
-// acc = (first ? 0 : acc) + a * b, node by node.
-__global__ __launch_bounds__(256) void product_accumulate_kernel(double* acc, const double* a, const double* b,
-                                                                 size_t n, int first) {
-  const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  acc[i] = (first ? 0.0 : acc[i]) + a[i] * b[i];
+// out = (first == 0 ? 0 : out) + sum over the count axes from first of U_a d_a, node by node, with d
+// and out padded and U three arrays of n nodes.
+__global__ __launch_bounds__(256) void advect_kernel(const double* U, const double* d, GridShape g, uint32_t pitch,
+                                                     size_t dist, int first, int count, double* out) {
+  const uint32_t cell = blockIdx.x * 256u + threadIdx.x;
+  if (cell >= g.n) return;
+  const size_t at = padded_index(cell, g, pitch);
+  double s = first == 0 ? 0.0 : out[at];
+  for (int a = 0; a < count; ++a) s += U[static_cast<size_t>(first + a) * g.n + cell] * d[a * dist + at];
+  out[at] = s;
 }
 
-// out = component comp of P x Q, with P and Q three consecutive arrays of n nodes.
-__global__ __launch_bounds__(256) void cross_component_kernel(const double* P, const double* Q, int comp, size_t n,
-                                                              double* out) {
-  const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int c = (comp + 1) % 3, d = (comp + 2) % 3;
-  out[i] = P[c * n + i] * Q[d * n + i] - P[d * n + i] * Q[c * n + i];
+// Components first .. first + count - 1 of P x Q, padded, with P and Q three consecutive arrays of n nodes.
+__global__ __launch_bounds__(256) void cross_kernel(const double* P, const double* Q, GridShape g, uint32_t pitch,
+                                                    size_t dist, int first, int count, double* out) {
+  const uint32_t cell = blockIdx.x * 256u + threadIdx.x;
+  if (cell >= g.n) return;
+  double p[3], q[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    p[c] = P[static_cast<size_t>(c) * g.n + cell];
+    q[c] = Q[static_cast<size_t>(c) * g.n + cell];
+  }
+  double* at = out + padded_index(cell, g, pitch);
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    if (c >= first && c < first + count) at[(c - first) * dist] = p[(c + 1) % 3] * q[(c + 2) % 3] - p[(c + 2) % 3] * q[(c + 1) % 3];
 }
 
-// Per-block shell sums of one transfer summand over the half spectrum (entries with
-// 0 < kx < nx - kx stand for their mirror too, whose summand is equal). kind 0:
-// sign Re[conj(X) Y]; kind 1: -sign Re[i Y (conj(B_hat) x q)_comp] = -sign Re[conj(B_hat) . (i q x Y e_comp)]
-// summed over comp by the caller, with B_hat the three transforms in Bh. Adds into partials
-// unless first is set. Binned without atomics, as shell_bin_kernel.
-__global__ __launch_bounds__(kBinThreads) void transfer_bin_kernel(int kind, const hipfftDoubleComplex* X,
+// Per-block shell sums of a transfer summand over the half spectrum (entries with 0 < kx < nx - kx
+// stand for their mirror too, whose summand is equal), summed over the components c0 .. c0 + count - 1
+// that Y holds. With x set, sign Re[conj(X_c) Y_c] into partials; with induction set,
+// induction times -Re[i Y_c (conj(B_hat) x q)_c] into ipartials, B_hat the three transforms in Bh. Added
+// to what is there unless c0 is 0. Binned without atomics, as shell_bin_kernel.
+__global__ __launch_bounds__(kBinThreads) void transfer_bin_kernel(const hipfftDoubleComplex* X, double sign,
                                                                    const hipfftDoubleComplex* Y,
-                                                                   const hipfftDoubleComplex* Bh, int comp,
-                                                                   double sign, int nx, int ny, int nz, int nshells,
-                                                                   double norm2, int first, double* partials) {
+                                                                   const hipfftDoubleComplex* Bh, double induction,
+                                                                   int c0, int count, HalfShape h, int nshells,
+                                                                   double norm2, double* partials, double* ipartials) {
   extern __shared__ double bins[];
-  for (int s = threadIdx.x; s < nshells; s += blockDim.x) bins[s] = 0.0;
-  __syncthreads();
-  const size_t nh = static_cast<size_t>(nz) * ny * (nx / 2 + 1);
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  for (size_t base = static_cast<size_t>(blockIdx.x) * blockDim.x; base < nh; base += stride) {
-    const size_t k = base + threadIdx.x;
-    int shell = -1;
-    double v = 0.0;
-    if (k < nh) {
-      int kx, ky, kz;
-      half_index(k, nx, ny, kx, ky, kz);
-      const double fx = kx, fy = signed_freq(ky, ny), fz = signed_freq(kz, nz);
-      shell = static_cast<int>(floor(sqrt(fx * fx + fy * fy + fz * fz) + 0.5));
-      if (shell < nshells) {
-        const hipfftDoubleComplex y = Y[k];
-        if (kind == 0) {
-          const hipfftDoubleComplex x = X[k];
-          v = sign * (x.x * y.x + x.y * y.y);
-        } else {
-          const double q[3] = {deriv_q(kx, nx), deriv_q(ky, ny), deriv_q(kz, nz)};
-          const int c = (comp + 1) % 3, d = (comp + 2) % 3;
-          const size_t plane = nh;
-          const hipfftDoubleComplex bc = Bh[c * plane + k], bd = Bh[d * plane + k];
-          // z = (conj(B_hat) x q)_comp = conj(B_c) q_d - conj(B_d) q_c
-          const double zr = bc.x * q[d] - bd.x * q[c];
-          const double zi = -bc.y * q[d] + bd.y * q[c];
-          // -Re[i y z] = Im[y z]
-          v = sign * (y.x * zi + y.y * zr);
+  double* ibins = bins + (X ? nshells : 0);
+  for (int s = threadIdx.x; s < (X ? nshells : 0) + (Bh ? nshells : 0); s += kBinThreads) bins[s] = 0.0;
+  for (uint32_t t = blockIdx.x; t < h.total; t += gridDim.x) {
+    const BinEntry e = bin_entry(t, h);
+    double v = 0.0, w = 0.0;
+    if (e.shell >= 0 && e.shell < nshells) {
+      const double q[3] = {deriv_q(e.kx, h.nx), deriv_q(e.ky, h.ny), deriv_q(e.kz, h.nz)};
+      hipfftDoubleComplex B[3];
+      if (Bh)
+        for (int c = 0; c < 3; ++c) B[c] = Bh[c * h.nh + e.k];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if (c < c0 || c >= c0 + count) continue;
+        const hipfftDoubleComplex y = Y[(c - c0) * h.nh + e.k];
+        if (X) {
+          const hipfftDoubleComplex x = X[c * h.nh + e.k];
+          v += x.x * y.x + x.y * y.y;
         }
-        const double mult = (kx == 0 || 2 * kx == nx) ? 1.0 : 2.0;
-        v = mult * v * norm2;
-      } else {
-        shell = -1;
+        if (Bh) {
+          // z = (conj(B_hat) x q)_c = conj(B_d) q_e - conj(B_e) q_d; -Re[i y z] = Im[y z]
+          const int d = (c + 1) % 3, f = (c + 2) % 3;
+          const double zr = B[d].x * q[f] - B[f].x * q[d];
+          const double zi = -B[d].y * q[f] + B[f].y * q[d];
+          w += y.x * zi + y.y * zr;
+        }
       }
+      const double mult = (e.kx == 0 || 2 * e.kx == h.nx) ? norm2 : 2.0 * norm2;
+      v *= sign * mult;
+      w *= induction * mult;
     }
-    bin_group(bins, shell, v);
+    if (X) bin_piece(bins, nshells, e.shell, v);
+    if (Bh) bin_piece(ibins, nshells, e.shell, w);
   }
-  __syncthreads();
-  for (int s = threadIdx.x; s < nshells; s += blockDim.x) {
-    double& out = partials[static_cast<size_t>(blockIdx.x) * nshells + s];
-    out = first ? bins[s] : out + bins[s];
-  }
+  if (X) bins_out(bins, nshells, c0 == 0, partials);
+  if (Bh) bins_out(ibins, nshells, c0 == 0, ipartials);
 }
 
 }  // namespace flame
@@ -905,7 +984,7 @@ hipError_t launch_reduce(const flame_ctx* c, double* partials, double* out) {
     return hipGetLastError();
   });
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(reduce_merge_kernel, dim3(1), dim3(64), 0, c->stream, partials, c->red_blocks,
+  hipLaunchKernelGGL(reduce_merge_kernel, dim3(1), dim3(kMergeGroups * FLAME_NRED), 0, c->stream, partials, c->red_blocks,
                      static_cast<double>(c->n), out);
   return hipGetLastError();
 }
@@ -1143,77 +1222,122 @@ flame_status flame_reduce_noalloc(flame_ctx* c, double* out) {
 
 namespace {
 
+HalfShape half_shape(const flame_ctx* c) {
+  HalfShape h;
+  h.nx = c->p.nx;
+  h.ny = c->p.ny;
+  h.nz = c->p.nz;
+  h.nxh = c->p.nx / 2 + 1;
+  h.pieces = static_cast<uint32_t>((h.nxh + kBinThreads - 1) / kBinThreads);
+  const size_t rows = static_cast<size_t>(h.ny) * h.nz;
+  h.total = static_cast<uint32_t>(rows * h.pieces);
+  h.nh = rows * h.nxh;
+  return h;
+}
+
+// Device memory that a context keeps: at least count elements in ptr, which holds have.
+template <typename T>
+bool keep_at_least(T*& ptr, size_t& have, size_t count) {
+  if (ptr && have >= count) return true;
+  if (ptr) (void)hipFree(ptr);
+  ptr = nullptr;
+  have = 0;
+  if (hipMalloc(&ptr, sizeof(T) * count) != hipSuccess) {
+    ptr = nullptr;
+    (void)hipGetLastError();  // clear the allocation error so later launch checks do not see it
+    return false;
+  }
+  have = count;
+  return true;
+}
+
+bool make_plan(flame_ctx* c, hipfftHandle& plan, bool& ok, hipfftType type) {
+  if (ok) return true;
+  int n[3] = {c->p.nz, c->p.ny, c->p.nx};
+  const int nxh = c->p.nx / 2 + 1;
+  int real[3] = {c->p.nz, c->p.ny, 2 * nxh}, half[3] = {c->p.nz, c->p.ny, nxh};
+  const bool many = c->spec_batch > 1;     // the distances only count then, and fit in an int (spectral_setup)
+  const int dist = many ? static_cast<int>(half_shape(c).nh) : 1, rdist = many ? 2 * dist : 1;
+  const bool fwd = type == HIPFFT_D2Z;
+  if (hipfftPlanMany(&plan, 3, n, fwd ? real : half, 1, fwd ? rdist : dist, fwd ? half : real, 1, fwd ? dist : rdist, type,
+                     c->spec_batch) != HIPFFT_SUCCESS)
+    return false;
+  ok = true;
+  return hipfftSetStream(plan, c->stream) == HIPFFT_SUCCESS;
+}
+
+// Workspace of the in-place transforms: three components at once (one batched transform, one pass over
+// the populations; 64^3 22 us against 3 x 12, from 256^3 on as fast as three), or one where the memory
+// for three is not there or an array spans too many values for the batch.
+flame_status spectral_setup(flame_ctx* c, int blocks, int terms, int nshells) {
+  const size_t nh = half_shape(c).nh;
+  if (!c->spec_work) {
+    c->spec_batch = 2 * nh <= 0x7fffffff ? 3 : 1;
+    if (!keep_at_least(c->spec_work, c->spec_work_size, c->spec_batch * nh)) {
+      c->spec_batch = 1;
+      if (!keep_at_least(c->spec_work, c->spec_work_size, nh)) return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
+    }
+  }
+  if (!make_plan(c, c->plan, c->plan_ok, HIPFFT_D2Z)) return fail(c, FLAME_E_HIP, "forward transform plan failed");
+  // block partials plus one row for their merged sums, per term
+  if (!keep_at_least(c->spec_partials, c->spec_partials_size, static_cast<size_t>(terms) * (blocks + 1) * nshells))
+    return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
+  return FLAME_OK;
+}
+
+// Fewer blocks for many shells: the block partials stay within 64 MiB a term.
+int bin_blocks(const HalfShape& h, int nshells) {
+  const uint32_t most = std::min<uint32_t>(kBinBlocksMax, (uint32_t(8) << 20) / static_cast<uint32_t>(nshells));
+  return static_cast<int>(std::min(most, h.total));
+}
+
+// Merge the block partials of the terms and copy the sums to the host.
+hipError_t merged_bins(flame_ctx* c, int blocks, int terms, int nshells, double* host) {
+  double* merged = c->spec_partials + static_cast<size_t>(terms) * blocks * nshells;
+  hipLaunchKernelGGL(bin_merge_kernel, dim3((nshells + kBinMergeShells - 1) / kBinMergeShells, terms),
+                     dim3(kBinMergeShells * kBinMergeGroups), 0, c->stream, c->spec_partials, blocks, nshells, merged);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(host, merged, sizeof(double) * terms * nshells, hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  return e;
+}
+
 // Energy (k2 = 0) or dissipation (k2 = 1) shell spectrum of u or B, summed over components.
 flame_status shell_spectrum(flame_ctx* c, int32_t field, int32_t nshells, int k2, double* e_k) {
   if (!c) return FLAME_E_INVAL;
   if (field != 0 && field != 1) return fail(c, FLAME_E_INVAL, "field must be 0 (u) or 1 (B)");
   if (nshells < 1 || nshells > kSpecShellsMax) return fail(c, FLAME_E_INVAL, "nshells out of range");
   if (!e_k) return fail(c, FLAME_E_INVAL, "e_k is NULL");
-  const int nx = c->p.nx, ny = c->p.ny, nz = c->p.nz;
-  const size_t nh = static_cast<size_t>(nz) * ny * (nx / 2 + 1);
-  // each buffer is checked on its own, and a failed allocation leaves its pointer null, so a call
-  // after an out-of-memory failure allocates again instead of launching on a missing buffer
-  if (!c->spec_real && hipMalloc(&c->spec_real, sizeof(double) * c->n) != hipSuccess) {
-    c->spec_real = nullptr;
-    (void)hipGetLastError();  // clear the allocation error so later launch checks do not see it
-    return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
-  }
-  if (!c->spec_cplx && hipMalloc(&c->spec_cplx, sizeof(hipfftDoubleComplex) * nh) != hipSuccess) {
-    c->spec_cplx = nullptr;
-    (void)hipGetLastError();  // clear the allocation error so later launch checks do not see it
-    return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
-  }
-  if (!c->plan_ok) {
-    if (hipfftPlan3d(&c->plan, nz, ny, nx, HIPFFT_D2Z) != HIPFFT_SUCCESS)
-      return fail(c, FLAME_E_HIP, "hipfftPlan3d failed");
-    c->plan_ok = true;
-    if (hipfftSetStream(c->plan, c->stream) != HIPFFT_SUCCESS) return fail(c, FLAME_E_HIP, "hipfftSetStream failed");
-  }
-  const int blocks = static_cast<int>(std::min<size_t>(kBinBlocksMax, blocks_for(nh, kBinThreads)));
-  if (!c->spec_partials || c->spec_blocks != blocks || c->spec_nshells < nshells) {
-    if (c->spec_partials) FLAME_HIP(c, hipFree(c->spec_partials));
-    c->spec_partials = nullptr;
-    c->spec_blocks = 0;
-    c->spec_nshells = 0;
-    // block partials plus one row for their merged sums
-    if (hipMalloc(&c->spec_partials, sizeof(double) * (static_cast<size_t>(blocks) + 1) * nshells) != hipSuccess) {
-      c->spec_partials = nullptr;
-      (void)hipGetLastError();  // clear the allocation error so later launch checks do not see it
-      return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
-    }
-    c->spec_blocks = blocks;
-    c->spec_nshells = nshells;
-  }
-  double* merged = c->spec_partials + static_cast<size_t>(blocks) * nshells;
-  std::vector<double> host(static_cast<size_t>(nshells));
+  const HalfShape h = half_shape(c);
+  const int blocks = bin_blocks(h, nshells);
+  const flame_status ready = spectral_setup(c, blocks, 1, nshells);
+  if (ready != FLAME_OK) return ready;
   for (int s = 0; s < nshells; ++s) e_k[s] = 0.0;
   const double norm2 = 1.0 / (static_cast<double>(c->n) * static_cast<double>(c->n));
-  for (int comp = 0; comp < 3; ++comp) {
-    hipError_t e = lattice_variant(c->p) ? variant_launch_component(c, field, comp, c->spec_real)
-                                         : by_storage(c, [&](auto tag) {
+  const uint32_t pitch = 2 * static_cast<uint32_t>(h.nxh);
+  double* real = reinterpret_cast<double*>(c->spec_work);
+  for (int c0 = 0; c0 < 3; c0 += c->spec_batch) {
+    hipError_t e = lattice_variant(c->p)
+                       ? variant_launch_components(c, field, c0, c->spec_batch, pitch, 2 * h.nh, real)
+                       : by_storage(c, [&](auto tag) {
       using S = decltype(tag);
-      hipLaunchKernelGGL(field_component_kernel<S>, dim3(blocks_for(c->n, 256)), dim3(256), 0, c->stream,
-                         make_aux<S>(c), field, comp, c->spec_real);
+      hipLaunchKernelGGL(field_kernel<S>, dim3(blocks_for(c->n, 256)), dim3(256), 0, c->stream, make_aux<S>(c),
+                         grid_shape(c->p, 256), field, c0, c->spec_batch, pitch, 2 * h.nh, real);
       return hipGetLastError();
     });
     if (e != hipSuccess) return fail(c, FLAME_E_HIP, std::string("field kernel: ") + hipGetErrorString(e));
-    if (hipfftExecD2Z(c->plan, c->spec_real, static_cast<hipfftDoubleComplex*>(c->spec_cplx)) != HIPFFT_SUCCESS)
+    if (hipfftExecD2Z(c->plan, real, c->spec_work) != HIPFFT_SUCCESS)
       return fail(c, FLAME_E_HIP, "hipfftExecD2Z failed");
     hipLaunchKernelGGL(shell_bin_kernel, dim3(blocks), dim3(kBinThreads), sizeof(double) * nshells, c->stream,
-                       static_cast<const hipfftDoubleComplex*>(c->spec_cplx), nx, ny, nz, nshells, norm2, k2,
-                       c->spec_partials);
+                       c->spec_work, c->spec_batch, h, nshells, norm2, k2, c0 == 0 ? 1 : 0, c->spec_partials);
     e = hipGetLastError();
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(bin_merge_kernel, dim3(blocks_for(static_cast<size_t>(nshells), 256), 1), dim3(256), 0,
-                         c->stream, c->spec_partials, blocks, nshells, merged);
-      e = hipGetLastError();
-    }
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(host.data(), merged, sizeof(double) * nshells, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return fail(c, FLAME_E_HIP, std::string("spectrum: ") + hipGetErrorString(e));
-    for (int s = 0; s < nshells; ++s) e_k[s] += host[s];
   }
+  std::vector<double> host(static_cast<size_t>(nshells));
+  const hipError_t e = merged_bins(c, blocks, 1, nshells, host.data());
+  if (e != hipSuccess) return fail(c, FLAME_E_HIP, std::string("spectrum: ") + hipGetErrorString(e));
+  for (int s = 0; s < nshells; ++s) e_k[s] = host[s];
   return FLAME_OK;
 }
 
@@ -1233,19 +1357,17 @@ flame_status flame_dissipation_spectrum(flame_ctx* c, int32_t field, int32_t nsh
 
 namespace {
 
-// Device buffers of one energy-transfer evaluation, released on every return once the work
-// queued on the stream (which may still use them on an error path) has finished.
-struct TransferScratch {
-  hipStream_t stream;
-  double* real = nullptr;              // U(3) B(3) J(3), a work field, the advection product
-  hipfftDoubleComplex* cplx = nullptr; // u_hat(3) B_hat(3), a work spectrum
-  double* partials = nullptr;          // 4 terms x blocks x nshells
-  explicit TransferScratch(hipStream_t s) : stream(s) {}
-  ~TransferScratch() {
-    (void)hipStreamSynchronize(stream);
-    if (real) (void)hipFree(real);
-    if (cplx) (void)hipFree(cplx);
-    if (partials) (void)hipFree(partials);
+// Node fields and transforms of the energy transfer, kept by the context up to this size (300^3) and
+// else released at the end of the call: allocating and freeing them took 30 ms of a 37 ms call at 192^3.
+constexpr size_t kTransferKeepBytes = size_t(4) << 30;
+struct TransferRelease {
+  flame_ctx* c;
+  ~TransferRelease() {
+    if (!c->transfer_work || c->transfer_size * sizeof(hipfftDoubleComplex) <= kTransferKeepBytes) return;
+    (void)hipStreamSynchronize(c->stream);   // work queued on an error path may still use it
+    (void)hipFree(c->transfer_work);
+    c->transfer_work = nullptr;
+    c->transfer_size = 0;
   }
 };
 
@@ -1254,41 +1376,30 @@ flame_status energy_transfer(flame_ctx* c, int32_t nshells, double* t_adv, doubl
   if (!c) return FLAME_E_INVAL;
   if (nshells < 1 || nshells > kSpecShellsMax) return fail(c, FLAME_E_INVAL, "nshells out of range");
   if (!t_adv || !t_lor || !t_ind) return fail(c, FLAME_E_INVAL, "an output array is NULL");
-  const int nx = c->p.nx, ny = c->p.ny, nz = c->p.nz;
   const size_t n = c->n;
-  const size_t nh = static_cast<size_t>(nz) * ny * (nx / 2 + 1);
-  if (!c->plan_ok) {
-    if (hipfftPlan3d(&c->plan, nz, ny, nx, HIPFFT_D2Z) != HIPFFT_SUCCESS)
-      return fail(c, FLAME_E_HIP, "hipfftPlan3d failed");
-    c->plan_ok = true;
-    if (hipfftSetStream(c->plan, c->stream) != HIPFFT_SUCCESS) return fail(c, FLAME_E_HIP, "hipfftSetStream failed");
-  }
-  if (!c->plan_inv_ok) {
-    if (hipfftPlan3d(&c->plan_inv, nz, ny, nx, HIPFFT_Z2D) != HIPFFT_SUCCESS)
-      return fail(c, FLAME_E_HIP, "hipfftPlan3d (inverse) failed");
-    c->plan_inv_ok = true;
-    if (hipfftSetStream(c->plan_inv, c->stream) != HIPFFT_SUCCESS)
-      return fail(c, FLAME_E_HIP, "hipfftSetStream failed");
-  }
-  const int blocks = static_cast<int>(std::min<size_t>(kBinBlocksMax, blocks_for(nh, kBinThreads)));
-  TransferScratch w(c->stream);
-  if (hipMalloc(&w.real, sizeof(double) * 11 * n) != hipSuccess) w.real = nullptr;
-  if (w.real && hipMalloc(&w.cplx, sizeof(hipfftDoubleComplex) * 7 * nh) != hipSuccess) w.cplx = nullptr;
-  // 4 terms of block partials, then the 4 merged rows
-  if (w.cplx && hipMalloc(&w.partials, sizeof(double) * 4 * (static_cast<size_t>(blocks) + 1) * nshells) != hipSuccess)
-    w.partials = nullptr;
-  if (!w.partials) {
-    (void)hipGetLastError();  // clear the allocation error so later launch checks do not see it
+  const HalfShape h = half_shape(c);
+  const GridShape g = grid_shape(c->p, 256);
+  const uint32_t pitch = 2 * static_cast<uint32_t>(h.nxh);
+  const size_t nh = h.nh, dist = 2 * nh;
+  const int blocks = bin_blocks(h, nshells), terms = t_hall ? 4 : 3;
+  const flame_status ready = spectral_setup(c, blocks, terms, nshells);
+  if (ready != FLAME_OK) return ready;
+  if (!make_plan(c, c->plan_inv, c->plan_inv_ok, HIPFFT_Z2D)) return fail(c, FLAME_E_HIP, "inverse transform plan failed");
+  const int nb = c->spec_batch;
+  TransferRelease release{c};
+  // u_hat(3), B_hat(3), then the real fields U(3), B(3), J(3) (in units of a complex value)
+  const size_t field3 = (3 * n + 1) / 2;
+  if (!keep_at_least(c->transfer_work, c->transfer_size, 6 * nh + std::max(3 * field3, field3 + 3 * nh)))
     return fail(c, FLAME_E_NOMEM, "energy transfer: device workspace");
-  }
-  double* U = w.real;
-  double* B = w.real + 3 * n;
-  double* J = w.real + 6 * n;
-  double* work = w.real + 9 * n;
-  double* adv = w.real + 10 * n;
-  hipfftDoubleComplex* Uh = w.cplx;
-  hipfftDoubleComplex* Bh = w.cplx + 3 * nh;
-  hipfftDoubleComplex* spec = w.cplx + 6 * nh;
+  hipfftDoubleComplex* Uh = c->transfer_work;
+  hipfftDoubleComplex* Bh = Uh + 3 * nh;
+  hipfftDoubleComplex* base = Uh + 6 * nh;
+  double* U = reinterpret_cast<double*>(base);
+  double* B = reinterpret_cast<double*>(base + field3);
+  double* J = reinterpret_cast<double*>(base + 2 * field3);
+  hipfftDoubleComplex* Ah = base + field3;      // the advection term, where B and J were
+  hipfftDoubleComplex* spec = c->spec_work;     // nb components
+  double* real = reinterpret_cast<double*>(spec);
   const unsigned gn = blocks_for(n, 256), gh = blocks_for(nh, 256);
   hipError_t e = lattice_variant(c->p) ? variant_launch_moments(c, nullptr, U, B, J, nullptr) : by_storage(c, [&](auto tag) {
     using S = decltype(tag);
@@ -1297,57 +1408,52 @@ flame_status energy_transfer(flame_ctx* c, int32_t nshells, double* t_adv, doubl
     return hipGetLastError();
   });
   if (e != hipSuccess) return fail(c, FLAME_E_HIP, std::string("energy transfer fields: ") + hipGetErrorString(e));
-  // forward transforms run on the work copy: the transform may overwrite its input
-  auto forward = [&](const double* src, hipfftDoubleComplex* dst) -> bool {
-    if (src != work && hipMemcpyAsync(work, src, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-      return false;
-    return hipfftExecD2Z(c->plan, work, dst) == HIPFFT_SUCCESS;
+  bool ok = true;
+  auto launched = [&] { return ok = ok && hipGetLastError() == hipSuccess; };
+  auto forward = [&](hipfftDoubleComplex* x) {
+    return ok = ok && hipfftExecD2Z(c->plan, reinterpret_cast<double*>(x), x) == HIPFFT_SUCCESS;
   };
   const double norm2 = 1.0 / (static_cast<double>(n) * static_cast<double>(n));
-  auto bin = [&](int kind, int term, const hipfftDoubleComplex* X, int comp, double sign, bool first) {
-    hipLaunchKernelGGL(transfer_bin_kernel, dim3(blocks), dim3(kBinThreads), sizeof(double) * nshells, c->stream,
-                       kind, X, spec, Bh, comp, sign, nx, ny, nz, nshells, norm2, first ? 1 : 0,
-                       w.partials + static_cast<size_t>(term) * blocks * nshells);
-    return hipGetLastError() == hipSuccess;
+  double* part[4];
+  for (int t = 0; t < 4; ++t) part[t] = c->spec_partials + static_cast<size_t>(t) * blocks * nshells;
+  auto bin = [&](const hipfftDoubleComplex* X, double sign, const hipfftDoubleComplex* Y, const hipfftDoubleComplex* Bx,
+                 double induction, int c0, double* p, double* ip) {
+    hipLaunchKernelGGL(transfer_bin_kernel, dim3(blocks), dim3(kBinThreads),
+                       sizeof(double) * nshells * ((X ? 1 : 0) + (Bx ? 1 : 0)), c->stream, X, sign, Y, Bx, induction, c0,
+                       nb, h, nshells, norm2, p, ip);
+    return launched();
   };
-  bool ok = true;
-  for (int b = 0; b < 3 && ok; ++b) ok = forward(U + b * n, Uh + b * nh) && forward(B + b * n, Bh + b * nh);
-  for (int b = 0; b < 3 && ok; ++b) {
-    // (U . grad) U_b, with grad U_b from the inverse transform of i q_a u_hat_b
-    for (int a = 0; a < 3 && ok; ++a) {
-      hipLaunchKernelGGL(spectral_derivative_kernel, dim3(gh), dim3(256), 0, c->stream, Uh + b * nh, nx, ny, nz, a,
-                         1.0 / static_cast<double>(n), spec);
-      ok = hipGetLastError() == hipSuccess && hipfftExecZ2D(c->plan_inv, spec, work) == HIPFFT_SUCCESS;
-      if (ok) {
-        hipLaunchKernelGGL(product_accumulate_kernel, dim3(gn), dim3(256), 0, c->stream, adv, U + a * n, work, n,
-                           a == 0 ? 1 : 0);
-        ok = hipGetLastError() == hipSuccess;
-      }
-    }
-    ok = ok && forward(adv, spec) && bin(0, 0, Uh + b * nh, b, 1.0, b == 0);
-    // Lorentz force (J x B)_b; the Hall term takes the same transform against conj(B_hat) x q
-    if (ok) {
-      hipLaunchKernelGGL(cross_component_kernel, dim3(gn), dim3(256), 0, c->stream, J, B, b, n, work);
-      ok = hipGetLastError() == hipSuccess && forward(work, spec) && bin(0, 1, Uh + b * nh, b, -1.0, b == 0);
-      if (ok && t_hall) ok = bin(1, 3, nullptr, b, -c->p.d_i, b == 0);
-    }
+  hipLaunchKernelGGL(pad_kernel, dim3(gn), dim3(256), 0, c->stream, U, g, pitch, dist, reinterpret_cast<double*>(Uh));
+  launched();
+  hipLaunchKernelGGL(pad_kernel, dim3(gn), dim3(256), 0, c->stream, B, g, pitch, dist, reinterpret_cast<double*>(Bh));
+  launched();
+  for (int b = 0; b < 6 && ok; b += nb) forward(Uh + b * nh);
+  for (int b = 0; b < 3 && ok; b += nb) {
     // induction: (U x B)_b, binned against conj(B_hat) x q
-    if (ok) {
-      hipLaunchKernelGGL(cross_component_kernel, dim3(gn), dim3(256), 0, c->stream, U, B, b, n, work);
-      ok = hipGetLastError() == hipSuccess && forward(work, spec) && bin(1, 2, nullptr, b, 1.0, b == 0);
+    hipLaunchKernelGGL(cross_kernel, dim3(gn), dim3(256), 0, c->stream, U, B, g, pitch, dist, b, nb, real);
+    launched() && forward(spec) && bin(nullptr, 0.0, spec, Bh, 1.0, b, nullptr, part[2]);
+    // Lorentz force (J x B)_b; the Hall term takes the same transform against conj(B_hat) x q. Both
+    // bins in one block need twice the LDS, which fits up to the largest shell count.
+    if (!ok) break;
+    hipLaunchKernelGGL(cross_kernel, dim3(gn), dim3(256), 0, c->stream, J, B, g, pitch, dist, b, nb, real);
+    launched() && forward(spec) &&
+        bin(Uh, -1.0, spec, t_hall ? Bh : nullptr, t_hall ? -c->p.d_i : 0.0, b, part[1], t_hall ? part[3] : nullptr);
+  }
+  // (U . grad) U_b, with grad U_b from the inverse transforms of i q_a u_hat_b
+  for (int b = 0; b < 3 && ok; ++b)
+    for (int a = 0; a < 3 && ok; a += nb) {
+      hipLaunchKernelGGL(spectral_derivative_kernel, dim3(gh), dim3(256), 0, c->stream, Uh + b * nh, h, divisor(h.nxh),
+                         divisor(h.ny), 1.0 / static_cast<double>(n), a, nb, spec);
+      if (!launched()) break;
+      ok = hipfftExecZ2D(c->plan_inv, spec, real) == HIPFFT_SUCCESS;
+      if (!ok) break;
+      hipLaunchKernelGGL(advect_kernel, dim3(gn), dim3(256), 0, c->stream, U, real, g, pitch, dist, a, nb,
+                         reinterpret_cast<double*>(Ah + b * nh));
+      launched();
     }
-  }
-  const int terms = t_hall ? 4 : 3;
-  double* merged = w.partials + static_cast<size_t>(4) * blocks * nshells;
-  if (ok) {
-    hipLaunchKernelGGL(bin_merge_kernel, dim3(blocks_for(static_cast<size_t>(nshells), 256), terms), dim3(256), 0,
-                       c->stream, w.partials, blocks, nshells, merged);
-    ok = hipGetLastError() == hipSuccess;
-  }
+  for (int b = 0; b < 3 && ok; b += nb) forward(Ah + b * nh) && bin(Uh, 1.0, Ah + b * nh, nullptr, 0.0, b, part[0], nullptr);
   std::vector<double> host(static_cast<size_t>(terms) * nshells);
-  if (ok) ok = hipMemcpyAsync(host.data(), merged, sizeof(double) * host.size(), hipMemcpyDeviceToHost,
-                              c->stream) == hipSuccess;
-  if (ok) ok = hipStreamSynchronize(c->stream) == hipSuccess;
+  if (ok) ok = merged_bins(c, blocks, terms, nshells, host.data()) == hipSuccess;
   if (!ok) {
     const hipError_t last = hipGetLastError();
     return fail(c, FLAME_E_HIP, std::string("energy transfer: a transform, copy or kernel launch failed (") +
@@ -1460,8 +1566,8 @@ void flame_destroy(flame_ctx* c) {
   if (c->plan_ok) hipfftDestroy(c->plan);
   if (c->plan_inv_ok) hipfftDestroy(c->plan_inv);
   if (c->red_partials) (void)hipFree(c->red_partials);
-  if (c->spec_real) (void)hipFree(c->spec_real);
-  if (c->spec_cplx) (void)hipFree(c->spec_cplx);
+  if (c->spec_work) (void)hipFree(c->spec_work);
+  if (c->transfer_work) (void)hipFree(c->transfer_work);
   if (c->spec_partials) (void)hipFree(c->spec_partials);
   delete c;
 }

@@ -35,11 +35,13 @@ struct flame_ctx {
   double* red_partials = nullptr;
   int red_blocks = 0;
   double* scratch = nullptr;   // this device's static reduction scratch (not owned)
-  double* spec_real = nullptr;
-  void* spec_cplx = nullptr;
-  double* spec_partials = nullptr;
-  int spec_blocks = 0;
-  int spec_nshells = 0;
+  hipfftDoubleComplex* spec_work = nullptr;   // spec_batch components, transformed in place
+  size_t spec_work_size = 0;
+  int spec_batch = 0;                         // components per transform (3, or 1 for want of memory)
+  double* spec_partials = nullptr;            // block partials and merged rows of the shell sums
+  size_t spec_partials_size = 0;
+  hipfftDoubleComplex* transfer_work = nullptr;   // fields and transforms of the energy transfer
+  size_t transfer_size = 0;
   hipfftHandle plan{};
   bool plan_ok = false;
   hipfftHandle plan_inv{};   // complex-to-real inverse, for spectral derivatives
@@ -168,7 +170,8 @@ hipError_t variant_launch_get(const flame_ctx* c, int deviations, double* dst);
 hipError_t variant_launch_gather(const flame_ctx* c, int deviations, const int64_t* cells, int64_t cnt, double* out);
 hipError_t variant_launch_set(const flame_ctx* c, int deviations, const double* src);
 hipError_t variant_launch_moments(const flame_ctx* c, double* rho, double* u, double* b, double* j, double* divb);
-hipError_t variant_launch_component(const flame_ctx* c, int field, int comp, double* out);
+hipError_t variant_launch_components(const flame_ctx* c, int field, int first, int count, uint32_t pitch, size_t dist,
+                                     double* out);
 hipError_t variant_launch_reduce(const flame_ctx* c, double* partials);
 // Rest populations of the lattice variants (host): f_rest[q], g_rest[3 m].
 void variant_rest(const flame_params& p, double* f_rest, double* g_rest);

@@ -408,9 +408,11 @@ __global__ __launch_bounds__(256) void variant_moments(VAux<S, FL, ML> a, double
   }
 }
 
-// One field component of u (field 0) or B (field 1) per node, for the spectra.
+// Components first .. first + count - 1 of u (field 0) or B (field 1), for the spectra: rows of pitch
+// values, components dist apart.
 template <typename S, typename FL, typename ML>
-__global__ __launch_bounds__(256) void variant_component(VAux<S, FL, ML> a, int field, int comp, double* out) {
+__global__ __launch_bounds__(256) void variant_components(VAux<S, FL, ML> a, int field, int first, int count,
+                                                          uint32_t pitch, size_t dist, double* out) {
   const size_t cell = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (cell >= a.v.n) return;
   int x, y, z;
@@ -418,10 +420,11 @@ __global__ __launch_bounds__(256) void variant_component(VAux<S, FL, ML> a, int 
   double r, U[3], Bf[3], b[3], Jf[3], d;
   bool fin;
   node_q(a, x, y, z, r, U, Bf, b, Jf, d, fin);
+  double* at = out + (static_cast<size_t>(z) * a.v.geo.ny + y) * pitch + x;
   // selected without a runtime index into the arrays (which would put them in per-thread private memory)
-  const double uc = comp == 0 ? U[0] : comp == 1 ? U[1] : U[2];
-  const double bc = comp == 0 ? Bf[0] : comp == 1 ? Bf[1] : Bf[2];
-  out[cell] = field == 0 ? uc : bc;
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    if (c >= first && c < first + count) at[static_cast<size_t>(c - first) * dist] = field == 0 ? U[c] : Bf[c];
 }
 
 // Block partials of the FP64 reductions in the slot order of flame_reduce (fixed grid, fixed
@@ -644,13 +647,14 @@ hipError_t variant_launch_moments(const flame_ctx* c, double* rho, double* u, do
   });
 }
 
-hipError_t variant_launch_component(const flame_ctx* c, int field, int comp, double* out) {
+hipError_t variant_launch_components(const flame_ctx* c, int field, int first, int count, uint32_t pitch, size_t dist,
+                                     double* out) {
   return dispatch(c->p, [&](auto stag, auto fltag, auto mltag) -> hipError_t {
     using S = decltype(stag);
     using FL = decltype(fltag);
     using ML = decltype(mltag);
-    hipLaunchKernelGGL((variant_component<S, FL, ML>), dim3(vblocks(c->n, 256)), dim3(256), 0, c->stream,
-                       make_vaux<S, FL, ML>(c), field, comp, out);
+    hipLaunchKernelGGL((variant_components<S, FL, ML>), dim3(vblocks(c->n, 256)), dim3(256), 0, c->stream,
+                       make_vaux<S, FL, ML>(c), field, first, count, pitch, dist, out);
     return hipGetLastError();
   });
 }
