@@ -138,18 +138,10 @@ struct AuxArgs {
   const typename Enc<S>::R* force_b;
   double b0[3];
   double alpha, omega_b;
-  int stencil;
   int emhd;     // electron MHD: J from the moments with the bulk velocity taken as zero
 };
 
-template <typename S>
-__device__ double field_fluct(const AuxArgs<S>& a, int comp, int x, int y, int z) {
-  double s = a.v.g(0, comp, x, y, z);
-  for (int i = 1; i < 7; ++i) s += a.v.g(i, comp, x, y, z);
-  if (a.force_b) s += 0.5 * static_cast<double>(a.force_b[static_cast<size_t>(comp) * a.v.n + a.v.node(x, y, z)]);
-  return s;
-}
-// the same with the magnetic addressing mode fixed at compile time (same order of the sum)
+// Component comp of b, with the magnetic addressing mode fixed at compile time.
 template <int M, typename S>
 __device__ __forceinline__ double field_fluct_m(const AuxArgs<S>& a, int comp, int x, int y, int z) {
   double s = a.v.template gm<M>(0, comp, x, y, z);
@@ -158,21 +150,7 @@ __device__ __forceinline__ double field_fluct_m(const AuxArgs<S>& a, int comp, i
   if (a.force_b) s += 0.5 * static_cast<double>(a.force_b[static_cast<size_t>(comp) * a.v.n + a.v.node(x, y, z)]);
   return s;
 }
-// J = central-difference curl of b at node (x, y, z)
-template <int M, typename S>
-__device__ __forceinline__ void curl_b(const AuxArgs<S>& a, int x, int y, int z, double (&J)[3]) {
-  const View<S>& v = a.v;
-  const int xp = wrap(x + 1, v.nx), xm = wrap(x - 1, v.nx);
-  const int yp = wrap(y + 1, v.ny), ym = wrap(y - 1, v.ny);
-  const int zp = wrap(z + 1, v.nz), zm = wrap(z - 1, v.nz);
-  J[0] = 0.5 * (field_fluct_m<M>(a, 2, x, yp, z) - field_fluct_m<M>(a, 2, x, ym, z))
-       - 0.5 * (field_fluct_m<M>(a, 1, x, y, zp) - field_fluct_m<M>(a, 1, x, y, zm));
-  J[1] = 0.5 * (field_fluct_m<M>(a, 0, x, y, zp) - field_fluct_m<M>(a, 0, x, y, zm))
-       - 0.5 * (field_fluct_m<M>(a, 2, xp, y, z) - field_fluct_m<M>(a, 2, xm, y, z));
-  J[2] = 0.5 * (field_fluct_m<M>(a, 1, xp, y, z) - field_fluct_m<M>(a, 1, xm, y, z))
-       - 0.5 * (field_fluct_m<M>(a, 0, x, yp, z) - field_fluct_m<M>(a, 0, x, ym, z));
-}
-
+// On the moment route (the curl-stencil route has stencil_march_kernel).
 template <typename S>
 __device__ NodeQ node_quantities(const AuxArgs<S>& a, int x, int y, int z) {
   NodeQ q;
@@ -207,16 +185,8 @@ __device__ NodeQ node_quantities(const AuxArgs<S>& a, int x, int y, int z) {
     q.b[c] = bb[c] + 0.5 * src;
     q.B[c] = a.b0[c] + q.b[c];
   }
-  if (!a.stencil) {
-    const double zero[3] = {0.0, 0.0, 0.0};
-    current_from_moments(lam, a.emhd ? zero : q.U, q.B, a.alpha, a.omega_b, q.J);
-  } else if (v.gmode == 0) {
-    curl_b<0>(a, x, y, z, q.J);
-  } else if (v.gmode == 1) {
-    curl_b<1>(a, x, y, z, q.J);
-  } else {
-    curl_b<2>(a, x, y, z, q.J);
-  }
+  const double zero[3] = {0.0, 0.0, 0.0};
+  current_from_moments(lam, a.emhd ? zero : q.U, q.B, a.alpha, a.omega_b, q.J);
   q.divb = -4.0 * a.omega_b * (lam[0][0] + lam[1][1] + lam[2][2]);
   return q;
 }
@@ -441,55 +411,212 @@ __global__ __launch_bounds__(256) void adjoint_fields_kernel(View<S> v, const ty
 constexpr int kRedThreads = 256;
 constexpr int kRedBlocksMax = 2048;
 
+__device__ __forceinline__ void reduce_add(const NodeQ& q, double (&acc)[FLAME_NRED]) {
+  const double u2 = q.U[0] * q.U[0] + q.U[1] * q.U[1] + q.U[2] * q.U[2];
+  acc[0] += 0.5 * u2;
+  acc[1] += 0.5 * (q.b[0] * q.b[0] + q.b[1] * q.b[1] + q.b[2] * q.b[2]);
+  acc[2] += q.U[0] * q.b[0] + q.U[1] * q.b[1] + q.U[2] * q.b[2];
+  acc[3] += q.J[0] * q.J[0] + q.J[1] * q.J[1] + q.J[2] * q.J[2];
+  acc[4] = fmax(acc[4], fabs(q.divb));
+  acc[5] += q.divb * q.divb;
+  acc[6] = fmax(acc[6], sqrt(u2));
+  acc[7] += (q.rho - 1.0) * (q.rho - 1.0);
+  acc[8] += q.finite ? 0.0 : 1.0;
+  acc[9] += q.rho;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    acc[10 + c] += q.rho * q.U[c];
+    acc[13 + c] += q.B[c];
+  }
+}
+// The block's partials from its threads' (tid of kRedThreads), by a fixed tree in sh.
+__device__ __forceinline__ void reduce_block(const double (&acc)[FLAME_NRED], double (*sh)[kRedThreads], unsigned tid,
+                                             double* partials) {
+#pragma unroll
+  for (int k = 0; k < FLAME_NRED; ++k) sh[k][tid] = acc[k];
+  __syncthreads();
+  for (unsigned s = kRedThreads / 2; s > 0; s >>= 1) {
+    if (tid < s) {
+      for (int k = 0; k < FLAME_NRED; ++k) {
+        const double o = sh[k][tid + s];
+        sh[k][tid] = (k == 4 || k == 6) ? fmax(sh[k][tid], o) : sh[k][tid] + o;
+      }
+    }
+    __syncthreads();
+  }
+  if (tid < FLAME_NRED) partials[blockIdx.x * FLAME_NRED + tid] = sh[tid][0];
+}
+
 // Per-block partials: sums in every slot except 4 and 6 (maxima). Fixed grid and a fixed
 // tree order make the result bitwise reproducible. Two blocks per CU at least: without that
 // bound the FP64 instantiation takes 261 VGPRs (one wave per SIMD) and runs slower than with
 // the few spills the bound costs.
 template <typename S>
 __global__ __launch_bounds__(kRedThreads, 2) void reduce_kernel(AuxArgs<S> a, double* partials) {
-  double acc[FLAME_NRED];
-  for (int k = 0; k < FLAME_NRED; ++k) acc[k] = 0.0;
+  double acc[FLAME_NRED] = {};
   const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
   for (size_t cell = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x; cell < a.v.n; cell += stride) {
     int x, y, z;
     node_xyz(cell, a.v.nx, a.v.ny, x, y, z);
-    const NodeQ q = node_quantities(a, x, y, z);
-    const double u2 = q.U[0] * q.U[0] + q.U[1] * q.U[1] + q.U[2] * q.U[2];
-    acc[0] += 0.5 * u2;
-    acc[1] += 0.5 * (q.b[0] * q.b[0] + q.b[1] * q.b[1] + q.b[2] * q.b[2]);
-    acc[2] += q.U[0] * q.b[0] + q.U[1] * q.b[1] + q.U[2] * q.b[2];
-    acc[3] += q.J[0] * q.J[0] + q.J[1] * q.J[1] + q.J[2] * q.J[2];
-    acc[4] = fmax(acc[4], fabs(q.divb));
-    acc[5] += q.divb * q.divb;
-    acc[6] = fmax(acc[6], sqrt(u2));
-    acc[7] += (q.rho - 1.0) * (q.rho - 1.0);
-    acc[8] += q.finite ? 0.0 : 1.0;
-    acc[9] += q.rho;
-    for (int c = 0; c < 3; ++c) {
-      acc[10 + c] += q.rho * q.U[c];
-      acc[13 + c] += q.B[c];
-    }
+    reduce_add(node_quantities(a, x, y, z), acc);
   }
   __shared__ double sh[FLAME_NRED][kRedThreads];
-  for (int k = 0; k < FLAME_NRED; ++k) sh[k][threadIdx.x] = acc[k];
-  __syncthreads();
-  for (unsigned s = kRedThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      for (int k = 0; k < FLAME_NRED; ++k) {
-        const double o = sh[k][threadIdx.x + s];
-        sh[k][threadIdx.x] = (k == 4 || k == 6) ? fmax(sh[k][threadIdx.x], o) : sh[k][threadIdx.x] + o;
+  reduce_block(acc, sh, threadIdx.x, partials);
+}
+
+// Node fields (REDUCE false) or reductions of the curl-stencil route. A workgroup marches tiles of 64 x 4
+// along z with b of four planes and of the ring around the tile in LDS, as the step does, so a node's
+// magnetic populations are read once for the curls of its neighbours: reading them at each of the six
+// neighbours took 84 more loads a node (192 x 160 x 176 FP32: fields 567 us, reductions 826). Every sum
+// has the order of node_quantities. Bound by HBM and the ring's re-reads.
+constexpr int kMarchRows = kRedThreads / 64;
+struct FieldPtrs {
+  double *rho, *u, *B, *J, *divb;
+};
+template <typename S, int FM, bool REDUCE>
+__global__ __launch_bounds__(kRedThreads) void stencil_march_kernel(AuxArgs<S> a, int planes, uint32_t items, FieldPtrs o,
+                                                                    double* partials) {
+  using E = Enc<S>;
+  constexpr Addr A = Addr::Global;
+  constexpr int TX = 64, TY = kMarchRows;
+  __shared__ double lds[4 * (TY + 2) * (TX + 2) * 3];
+  static_assert(sizeof(lds) >= sizeof(double) * FLAME_NRED * kRedThreads, "the block tree reuses the tile's LDS");
+  double(*sb)[TY + 2][TX + 2][3] = reinterpret_cast<double(*)[TY + 2][TX + 2][3]>(lds);
+  const View<S>& v = a.v;
+  const int nx = v.nx, ny = v.ny, nz = v.nz;
+  const uint32_t plane = static_cast<uint32_t>(nx) * ny;
+  const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
+  const uint32_t gx = (nx + TX - 1) / TX, gy = (ny + TY - 1) / TY;
+  double acc[FLAME_NRED] = {};
+  for (uint32_t it = gridDim.x == items ? logical_index(items) : blockIdx.x; it < items; it += gridDim.x) {
+    const int x0 = (it % gx) * TX, y0 = (it / gx % gy) * TY, z_begin = it / (gx * gy) * planes;
+    const int w = min(TX, nx - x0), h = min(TY, ny - y0), z_end = min(nz, z_begin + planes);
+    const bool active = lx < w && ly < h;
+    const Rows rw(active ? x0 + lx : 0, active ? y0 + ly : 0, nx, ny);
+    auto pull = [&](const Rows& r, const Planes& pl, int i, int c) {
+      const uint32_t off = r.at(-xim(i, 0), -xim(i, 1)) + pl.at(-xim(i, 2));
+      return static_cast<double>(ld<A>(v.G + static_cast<size_t>(i * 3 + c) * v.stride, off)) / E::mscale(i);
+    };
+    auto half_src = [&](uint32_t cell, int c) {
+      return a.force_b ? 0.5 * static_cast<double>(a.force_b[static_cast<size_t>(c) * v.n + cell]) : 0.0;
+    };
+    // b of the node's own populations into slot; their trace of Lambda and finiteness
+    auto own = [&](int slot, const Planes& pl, double& tr, bool& fin) {
+      double g[kM];
+#pragma unroll
+      for (int i = 0; i < 7; ++i)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) g[i * 3 + c] = pull(rw, pl, i, c);
+      fin = true;
+#pragma unroll
+      for (int q = 0; q < kM; ++q) fin = fin && isfinite(g[q]);
+      double b[3], lam[3][3];
+      magnetic_moments(g, b, lam);
+      tr = lam[0][0] + lam[1][1] + lam[2][2];
+      const uint32_t cell = rw.at(0, 0) + pl.at(0);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sb[slot][ly + 1][lx + 1][c] = a.force_b ? b[c] + half_src(cell, c) : b[c];
+    };
+    // the ring: y-neighbours enter through B_x and B_z, x-neighbours through B_y and B_z
+    auto ring = [&](int slot, const Planes& pl) {
+      for (int task = threadIdx.x; task < 2 * w + 2 * h; task += kRedThreads) {
+        const bool side = task >= 2 * w;
+        const int t = side ? task - 2 * w : task, len = side ? h : w, at = t < len ? t : t - len;
+        const int rx = side ? (t < h ? -1 : w) : at, ry = side ? at : (t < w ? -1 : h);
+        const Rows rr(wrap(x0 + rx, nx), wrap(y0 + ry, ny), nx, ny);
+        const uint32_t cell = rr.at(0, 0) + pl.at(0);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int c = k == 1 ? 2 : side ? 1 : 0;
+          double b = pull(rr, pl, 0, c);
+#pragma unroll
+          for (int i = 1; i < 7; ++i) b += pull(rr, pl, i, c);
+          sb[slot][ry + 1][rx + 1][c] = a.force_b ? b + half_src(cell, c) : b;
+        }
       }
+    };
+    double tr = 0, tr_next = 0;
+    bool fin = true, fin_next = true;
+    const Planes p0(z_begin, nz, plane);
+    if (active) {
+      own(0, Planes(wrap(z_begin - 1, nz), nz, plane), tr, fin);
+      own(1, p0, tr_next, fin_next);
     }
-    __syncthreads();
+    ring(1, p0);
+    int prev = 0, cur = 1, next = 2, spare = 3;
+    for (int z = z_begin; z < z_end; ++z) {
+      const Planes pl(z, nz, plane), pn(wrap(z + 1, nz), nz, plane);
+      const uint32_t cell = rw.at(0, 0) + pl.at(0);
+      tr = tr_next;
+      fin = fin_next;
+      NodeQ q;
+      if (active) own(next, pn, tr_next, fin_next);
+      ring(next, pn);
+      if (active) {
+        double drho = 0, j[3] = {0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+          const uint32_t off = FM == 0 ? cell : rw.at(-cq(i, 0), -cq(i, 1)) + pl.at(-cq(i, 2));
+          const double f =
+              static_cast<double>(ld<A>(v.F + static_cast<size_t>(FM == 1 ? oppq(i) : i) * v.stride, off)) / E::fscale(i);
+          fin = fin && isfinite(f);
+          drho += f;
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            if (cq(i, c) != 0) j[c] += cq(i, c) * f;
+        }
+        q.rho = 1.0 + drho;
+        q.finite = fin;
+        q.divb = -4.0 * a.omega_b * tr;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const double F = a.force_u ? static_cast<double>(a.force_u[static_cast<size_t>(c) * v.n + cell]) : 0.0;
+          q.U[c] = (j[c] + 0.5 * F) / q.rho;
+        }
+      }
+      __syncthreads();   // a slot is rewritten two planes after it was last read: one barrier a plane
+      if (active) {
+        const double(&P)[TY + 2][TX + 2][3] = sb[prev];
+        const double(&C)[TY + 2][TX + 2][3] = sb[cur];
+        const double(&N)[TY + 2][TX + 2][3] = sb[next];
+        const int px = lx + 1, py = ly + 1;
+        q.J[0] = 0.5 * (C[py + 1][px][2] - C[py - 1][px][2]) - 0.5 * (N[py][px][1] - P[py][px][1]);
+        q.J[1] = 0.5 * (N[py][px][0] - P[py][px][0]) - 0.5 * (C[py][px + 1][2] - C[py][px - 1][2]);
+        q.J[2] = 0.5 * (C[py][px + 1][1] - C[py][px - 1][1]) - 0.5 * (C[py + 1][px][0] - C[py - 1][px][0]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          q.b[c] = C[py][px][c];
+          q.B[c] = a.b0[c] + q.b[c];
+        }
+        if (REDUCE) {
+          reduce_add(q, acc);
+        } else {
+          if (o.rho) o.rho[cell] = q.rho;
+          if (o.divb) o.divb[cell] = q.divb;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            if (o.u) o.u[c * v.n + cell] = q.U[c];
+            if (o.B) o.B[c * v.n + cell] = q.B[c];
+            if (o.J) o.J[c * v.n + cell] = q.J[c];
+          }
+        }
+      }
+      const int t = prev;
+      prev = cur;
+      cur = next;
+      next = spare;
+      spare = t;
+    }
+    __syncthreads();   // the next item, or the block tree, rewrites the LDS
   }
-  if (threadIdx.x < FLAME_NRED) partials[blockIdx.x * FLAME_NRED + threadIdx.x] = sh[threadIdx.x][0];
+  if (REDUCE) reduce_block(acc, reinterpret_cast<double(*)[kRedThreads]>(lds), threadIdx.x, partials);
 }
 
 // Fixed-order merge of the block partials of reduce_kernel into the FLAME_NRED results: thread
 // (g, k) runs over the blocks g, g + 64, ... in order for slot k (sums; maxima for slots 4 and 6), the
 // 64 groups meet in a fixed tree, and the slot is normalised as flame_reduce documents (node
 // averages, rms, plain sums and maxima). One thread per slot over all 2048 blocks took 700 us, as
-// long as the reduction of 200^3 nodes; this takes 7.
+// long as the reduction of 200^3 nodes; this takes 12.
 constexpr int kMergeGroups = 64;
 __global__ __launch_bounds__(kMergeGroups * FLAME_NRED) void reduce_merge_kernel(const double* partials, int blocks,
                                                                                  double n, double* out) {
@@ -497,6 +624,7 @@ __global__ __launch_bounds__(kMergeGroups * FLAME_NRED) void reduce_merge_kernel
   const int k = threadIdx.x % FLAME_NRED, g = threadIdx.x / FLAME_NRED;
   const bool max_slot = k == 4 || k == 6;
   double acc = 0.0;
+#pragma unroll 8
   for (int b = g; b < blocks; b += kMergeGroups) {
     const double v = partials[static_cast<size_t>(b) * FLAME_NRED + k];
     acc = max_slot ? fmax(acc, v) : acc + v;
@@ -668,9 +796,10 @@ __global__ __launch_bounds__(kBinThreads) void shell_bin_kernel(const hipfftDoub
 }
 
 // out[t][s] = sum over blocks of partials[t][block][s] (terms t < gridDim.y): thread (g, s) runs
-// over the blocks g, g + 16, ... in order, the 16 groups meet in a fixed tree.
+// over the blocks g, g + 64, ... in order, the 64 groups meet in a fixed tree (4096 blocks of 129 shells:
+// 16 groups 79 us, 64 groups 20).
 constexpr int kBinMergeShells = 16;
-constexpr int kBinMergeGroups = 16;
+constexpr int kBinMergeGroups = 64;
 __global__ __launch_bounds__(kBinMergeShells * kBinMergeGroups) void bin_merge_kernel(const double* partials, int blocks,
                                                                                       int nshells, double* out) {
   __shared__ double sh[kBinMergeGroups][kBinMergeShells];
@@ -680,6 +809,7 @@ __global__ __launch_bounds__(kBinMergeShells * kBinMergeGroups) void bin_merge_k
   double acc = 0.0;
   if (s < nshells) {
     const double* p = partials + t * blocks * nshells + s;
+#pragma unroll 8
     for (int b = g; b < blocks; b += kBinMergeGroups) acc += p[static_cast<size_t>(b) * nshells];
   }
   sh[g][l] = acc;
@@ -899,7 +1029,6 @@ AuxArgs<S> make_aux(const flame_ctx* c) {
   for (int i = 0; i < 3; ++i) a.b0[i] = c->p.b0[i];
   a.alpha = c->p.d_i;
   a.omega_b = c->omega_b;
-  a.stencil = c->p.jmode == FLAME_J_STENCIL;
   a.emhd = c->p.magnetic == FLAME_MAGNETIC_EMHD;
   return a;
 }
@@ -974,17 +1103,65 @@ hipError_t scratch_address(int device, double** out) {
 // Lattice sound speed c_s = 1/sqrt(3): the flame_reduce guard on max |u|.
 constexpr double kSoundSpeed = 0.57735026918962576;
 
-// The reductions of the current state: block partials into partials (c->red_blocks x FLAME_NRED
-// doubles), merged in a fixed order into out (FLAME_NRED doubles, device). Asynchronous.
-hipError_t launch_reduce(const flame_ctx* c, double* partials, double* out) {
-  hipError_t e = lattice_variant(c->p) ? variant_launch_reduce(c, partials) : by_storage(c, [&](auto tag) {
+// Node fields (partials null) or block partials of the stencil route; blocks returns the partials' rows.
+hipError_t launch_stencil_march(const flame_ctx* c, const FieldPtrs& o, double* partials, int& blocks) {
+  const uint32_t tiles = static_cast<uint32_t>((c->p.nx + 63) / 64) * ((c->p.ny + kMarchRows - 1) / kMarchRows);
+  const int planes = march_planes(tiles, c->p.nz, static_cast<int64_t>(c->cus) * 4, 32);
+  const uint32_t items = tiles * ((c->p.nz + planes - 1) / planes);
+  blocks = static_cast<int>(partials ? std::min<uint32_t>(items, kRedBlocksMax) : items);
+  return by_storage(c, [&](auto tag) {
     using S = decltype(tag);
-    hipLaunchKernelGGL(reduce_kernel<S>, dim3(c->red_blocks), dim3(kRedThreads), 0, c->stream, make_aux<S>(c),
-                       partials);
+    const AuxArgs<S> a = make_aux<S>(c);
+    auto go = [&](auto mode) {
+      constexpr int FM = decltype(mode)::value;
+      if (partials)
+        hipLaunchKernelGGL((stencil_march_kernel<S, FM, true>), dim3(blocks), dim3(kRedThreads), 0, c->stream, a, planes,
+                           items, o, partials);
+      else
+        hipLaunchKernelGGL((stencil_march_kernel<S, FM, false>), dim3(blocks), dim3(kRedThreads), 0, c->stream, a, planes,
+                           items, o, partials);
+    };
+    if (a.v.fmode == 0) go(std::integral_constant<int, 0>{});
+    else if (a.v.fmode == 1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 2>{});
     return hipGetLastError();
   });
+}
+
+// Node fields of the current state, each array optional. Asynchronous.
+hipError_t launch_moments(const flame_ctx* c, double* rho, double* u, double* b, double* j, double* divb) {
+  if (lattice_variant(c->p)) return variant_launch_moments(c, rho, u, b, j, divb);
+  if (c->p.jmode == FLAME_J_STENCIL) {
+    int blocks;
+    return launch_stencil_march(c, FieldPtrs{rho, u, b, j, divb}, nullptr, blocks);
+  }
+  return by_storage(c, [&](auto tag) {
+    using S = decltype(tag);
+    hipLaunchKernelGGL(moments_kernel<S>, dim3(blocks_for(c->n, 256)), dim3(256), 0, c->stream, make_aux<S>(c), rho, u, b,
+                       j, divb);
+    return hipGetLastError();
+  });
+}
+
+// The reductions of the current state: block partials into partials (at most kRedBlocksMax x
+// FLAME_NRED doubles), merged in a fixed order into out (FLAME_NRED doubles, device). Asynchronous.
+hipError_t launch_reduce(const flame_ctx* c, double* partials, double* out) {
+  int blocks = c->red_blocks;
+  hipError_t e;
+  if (lattice_variant(c->p)) {
+    e = variant_launch_reduce(c, partials);
+  } else if (c->p.jmode == FLAME_J_STENCIL) {
+    e = launch_stencil_march(c, FieldPtrs{}, partials, blocks);
+  } else {
+    e = by_storage(c, [&](auto tag) {
+      using S = decltype(tag);
+      hipLaunchKernelGGL(reduce_kernel<S>, dim3(c->red_blocks), dim3(kRedThreads), 0, c->stream, make_aux<S>(c),
+                         partials);
+      return hipGetLastError();
+    });
+  }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(reduce_merge_kernel, dim3(1), dim3(kMergeGroups * FLAME_NRED), 0, c->stream, partials, c->red_blocks,
+  hipLaunchKernelGGL(reduce_merge_kernel, dim3(1), dim3(kMergeGroups * FLAME_NRED), 0, c->stream, partials, blocks,
                      static_cast<double>(c->n), out);
   return hipGetLastError();
 }
@@ -1109,7 +1286,7 @@ flame_status flame_init(const flame_params* p, const double* u, const double* b,
   }
   c->red_blocks = static_cast<int>(std::min<size_t>(kRedBlocksMax, blocks_for(c->n, kRedThreads)));
   // block partials of the reductions plus one row for their merged results
-  if (hipMalloc(&c->red_partials, sizeof(double) * FLAME_NRED * (std::max(c->red_blocks, 1) + 1)) != hipSuccess) {
+  if (hipMalloc(&c->red_partials, sizeof(double) * FLAME_NRED * (kRedBlocksMax + 1)) != hipSuccess) {
     c->err = "hipMalloc of reduction scratch failed";
     return bail(FLAME_E_NOMEM);
   }
@@ -1183,12 +1360,7 @@ flame_status flame_step(flame_ctx* c, int64_t nsteps) {
 
 flame_status flame_moments(flame_ctx* c, double* rho, double* u, double* b, double* j, double* divb) {
   if (!c) return FLAME_E_INVAL;
-  hipError_t e = lattice_variant(c->p) ? variant_launch_moments(c, rho, u, b, j, divb) : by_storage(c, [&](auto tag) {
-    using S = decltype(tag);
-    hipLaunchKernelGGL(moments_kernel<S>, dim3(blocks_for(c->n, 256)), dim3(256), 0, c->stream,
-                       make_aux<S>(c), rho, u, b, j, divb);
-    return hipGetLastError();
-  });
+  const hipError_t e = launch_moments(c, rho, u, b, j, divb);
   if (e != hipSuccess) return fail(c, FLAME_E_HIP, std::string("moments kernel: ") + hipGetErrorString(e));
   return FLAME_OK;
 }
@@ -1196,7 +1368,7 @@ flame_status flame_moments(flame_ctx* c, double* rho, double* u, double* b, doub
 flame_status flame_reduce(flame_ctx* c, double* out) {
   if (!c || !out) return c ? fail(c, FLAME_E_INVAL, "out is NULL") : FLAME_E_INVAL;
   // block partials, then the merged results behind them in the same scratch
-  double* merged = c->red_partials + static_cast<size_t>(c->red_blocks) * FLAME_NRED;
+  double* merged = c->red_partials + static_cast<size_t>(kRedBlocksMax) * FLAME_NRED;
   hipError_t e = launch_reduce(c, c->red_partials, merged);
   if (e != hipSuccess) return fail(c, FLAME_E_HIP, std::string("reduce kernel: ") + hipGetErrorString(e));
   FLAME_HIP(c, hipMemcpyAsync(out, merged, sizeof(double) * FLAME_NRED, hipMemcpyDeviceToHost, c->stream));
@@ -1401,12 +1573,7 @@ flame_status energy_transfer(flame_ctx* c, int32_t nshells, double* t_adv, doubl
   hipfftDoubleComplex* spec = c->spec_work;     // nb components
   double* real = reinterpret_cast<double*>(spec);
   const unsigned gn = blocks_for(n, 256), gh = blocks_for(nh, 256);
-  hipError_t e = lattice_variant(c->p) ? variant_launch_moments(c, nullptr, U, B, J, nullptr) : by_storage(c, [&](auto tag) {
-    using S = decltype(tag);
-    hipLaunchKernelGGL(moments_kernel<S>, dim3(gn), dim3(256), 0, c->stream, make_aux<S>(c), nullptr, U, B, J,
-                       nullptr);
-    return hipGetLastError();
-  });
+  const hipError_t e = launch_moments(c, nullptr, U, B, J, nullptr);
   if (e != hipSuccess) return fail(c, FLAME_E_HIP, std::string("energy transfer fields: ") + hipGetErrorString(e));
   bool ok = true;
   auto launched = [&] { return ok = ok && hipGetLastError() == hipSuccess; };

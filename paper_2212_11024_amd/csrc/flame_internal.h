@@ -146,6 +146,24 @@ inline GridShape grid_shape(const flame_params& p, unsigned threads) {
           threads, static_cast<uint32_t>((n + threads - 1) / threads)};
 }
 
+// Planes per workgroup of a kernel that marches tiles along z: the power of two up to most that a grid
+// finishes first with, counting rounds of resident workgroups times the planes of one, whose prologue
+// costs about 3/4 of a plane. Long chunks waste less in prologues, short ones fill the chip.
+inline int march_planes(int64_t tiles, int nz, int64_t resident, int most) {
+  resident = std::max<int64_t>(resident, 1);
+  int best = 1;
+  double least = 0;
+  for (int planes = 1; planes <= most; planes *= 2) {
+    const int64_t groups = tiles * ((nz + planes - 1) / planes);
+    const double cost = static_cast<double>((groups + resident - 1) / resident) * (std::min(planes, nz) + 0.75);
+    if (planes == 1 || cost <= least) {
+      least = cost;
+      best = planes;
+    }
+  }
+  return best;
+}
+
 // Threads per block of the node-local kernels: a row of nx nodes rounded up to whole wavefronts, at
 // most 256 (their launch bound), whatever FLAME_ROW_THREADS asks for. The blocks of the kernels that
 // split the grid by linear node index need not hold whole rows; there short rows only make blocks

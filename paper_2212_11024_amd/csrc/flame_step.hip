@@ -365,26 +365,13 @@ __global__ __launch_bounds__(kTX * kTY) void step_zmarch(StepArgs<S> a) {
   }
 }
 
-// Planes per workgroup of the stencil kernel: the power of two up to 64 that a grid finishes first
-// with, counting rounds of resident workgroups (per_cu on each compute unit: its registers hold two
-// in FP32 and FP16, one in FP64) times the planes of one, whose prologue costs about 3/4 of a plane.
-// Long chunks waste less in prologues, short ones fill the chip: with 32 planes everywhere 64^3 FP32
-// ran 32 workgroups and took 295 us for two steps against 52, 128^3 509 against 366, 32^3 275 against
+// Planes per workgroup of the stencil kernel, per_cu workgroups resident on a compute unit (its
+// registers hold two in FP32 and FP16, one in FP64). With 32 planes everywhere 64^3 FP32 ran 32
+// workgroups and took 295 us for two steps against 52, 128^3 509 against 366, 32^3 275 against
 // 31; at 256^3 64 planes are the best (FP32 2.98 against 3.02 ms for 32 and 3.09 for 8, FP64 5.62, 5.75, 5.92).
 static int zchunk_planes(const flame_ctx* c, int per_cu) {
-  const int64_t tiles = static_cast<int64_t>((c->p.nx + kTX - 1) / kTX) * ((c->p.ny + kTY - 1) / kTY);
-  const int64_t resident = static_cast<int64_t>(std::max(c->cus, 1)) * per_cu;
-  int best = 1;
-  double least = 0;
-  for (int planes = 1; planes <= 64; planes *= 2) {
-    const int64_t groups = tiles * ((c->p.nz + planes - 1) / planes);
-    const double cost = static_cast<double>((groups + resident - 1) / resident) * (std::min(planes, c->p.nz) + 0.75);
-    if (planes == 1 || cost <= least) {
-      least = cost;
-      best = planes;
-    }
-  }
-  return best;
+  return march_planes(static_cast<int64_t>((c->p.nx + kTX - 1) / kTX) * ((c->p.ny + kTY - 1) / kTY), c->p.nz,
+                      static_cast<int64_t>(c->cus) * per_cu, 64);
 }
 
 template <typename S, bool SAVE, int MODEL, Addr A>
