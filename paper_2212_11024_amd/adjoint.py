@@ -34,20 +34,17 @@ def spectral_gradient(v: torch.Tensor) -> torch.Tensor:
     nz, ny, nx = v.shape[1:]
     dev, dt = v.device, v.dtype
 
-    def k(n):
-        f = torch.fft.fftfreq(n, d=1.0 / n, device=dev, dtype=dt)
+    def k(n, freq=torch.fft.fftfreq):
+        f = freq(n, d=0.5 / math.pi, device=dev, dtype=dt)
         if n % 2 == 0:
             f[n // 2] = 0.0           # the Nyquist mode has no well-defined derivative
-        return 2.0 * math.pi * f / n
+        return f
 
-    kx = k(nx).view(1, 1, nx)
-    ky = k(ny).view(1, ny, 1)
-    kz = k(nz).view(nz, 1, 1)
-    vh = torch.fft.fftn(v, dim=(1, 2, 3))
-    out = []
-    for ka in (kx, ky, kz):
-        out.append(torch.fft.ifftn(1j * ka * vh, dim=(1, 2, 3)).real)
-    return torch.stack(out)
+    # real transforms (half the spectrum), the three axes back in one batch: with complex ones and one
+    # inverse per axis the gradients took 0.8 ms of a 2.1 ms rollout of 12 steps at 48^3
+    vh = torch.fft.rfftn(v, dim=(1, 2, 3))
+    ik = (k(nx, torch.fft.rfftfreq).view(1, 1, -1), k(ny).view(1, ny, 1), k(nz).view(nz, 1, 1))
+    return torch.fft.irfftn(torch.stack([1j * ka * vh for ka in ik]), s=(nz, ny, nx), dim=(2, 3, 4))
 
 
 def shell_spectrum(v: torch.Tensor, nshells: int) -> torch.Tensor:
