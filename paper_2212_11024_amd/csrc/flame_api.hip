@@ -42,19 +42,8 @@ struct View {
   __device__ size_t node(int x, int y, int z) const {
     return (static_cast<size_t>(z) * ny + y) * nx + x;
   }
-  // element of F / G holding canonical population i (component c) of node (x, y, z), for the
-  // trace export
-  __device__ size_t fidx(int i, int x, int y, int z) const {
-    return fmode == 0 ? static_cast<size_t>(i) * stride + node(x, y, z)
-                      : static_cast<size_t>(fmode == 1 ? oppq(i) : i) * stride +
-                            node(wrap(x - cq(i, 0), nx), wrap(y - cq(i, 1), ny), wrap(z - cq(i, 2), nz));
-  }
-  __device__ size_t gidx(int i, int c, int x, int y, int z) const {
-    return gmode == 0 ? static_cast<size_t>(i * 3 + c) * stride + node(x, y, z)
-                      : static_cast<size_t>((gmode == 1 ? oppm(i) : i) * 3 + c) * stride +
-                            node(wrap(x - xim(i, 0), nx), wrap(y - xim(i, 1), ny), wrap(z - xim(i, 2), nz));
-  }
-  // the same with the addressing mode fixed at compile time (no branch per access, so that a
+  // canonical population i (component c) of node (x, y, z), with the addressing mode fixed at compile
+  // time (no branch per access, so that a
   // node's loads can all be in flight together)
   template <int M>
   __device__ double fm(int i, int x, int y, int z) const {
@@ -316,21 +305,30 @@ __global__ __launch_bounds__(256) void set_kernel(S* F, S* G, size_t n, size_t s
     }
 }
 
-// Trace lattice of the current state (two-lattice pull layout, node stride n): canonical
-// population i of node x goes to slot i at x - c_i, where a pull step at x reads it. The stored
-// values are moved without decoding, so the copy is exact.
-template <typename S>
-__global__ __launch_bounds__(256) void export_kernel(View<S> v, S* lat) {
-  const size_t cell = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (cell >= v.n) return;
-  int x, y, z;
-  node_xyz(cell, v.nx, v.ny, x, y, z);
-  for (int i = 0; i < kQ; ++i)
-    lat[static_cast<size_t>(i) * v.n + v.node(wrap(x - cq(i, 0), v.nx), wrap(y - cq(i, 1), v.ny),
-                                              wrap(z - cq(i, 2), v.nz))] = v.F[v.fidx(i, x, y, z)];
+// Trace lattice of the current state (two-lattice pull layout, node stride n): slot i at x holds
+// canonical population i of node x + c_i, which a pull step there reads. In place that is slot i at
+// x + c_i after an even number of steps (M 0) and slot opp(i) at x after an odd one (M 1). The stored
+// values are moved without decoding, so the copy is exact. Bound by HBM; written in whole lines (128^3 FP32
+// 257 us when each node wrote to x - c_i through 64-bit indices, 204 now; 48^3 FP64 27 and 17).
+template <typename S, int M>
+__global__ __launch_bounds__(kRowThreadsMax) void export_kernel(const S* F, const S* G, size_t stride, GridShape shape,
+                                                                size_t n, S* lat) {
+  constexpr Addr A = Addr::Global;
+  uint32_t cell;
+  if (!own_cell(shape, cell)) return;
+  const NodeAt at = NodeAt::of(cell, shape);
+#pragma unroll
+  for (int i = 0; i < kQ; ++i) {
+    const uint32_t off = M == 0 ? at.rw.at(cq(i, 0), cq(i, 1)) + at.pl.at(cq(i, 2)) : cell;
+    st<A>(lat + static_cast<size_t>(i) * n, cell, ld<A>(F + static_cast<size_t>(M == 0 ? i : oppq(i)) * stride, off));
+  }
+#pragma unroll
   for (int i = 0; i < 7; ++i) {
-    const size_t dn = v.node(wrap(x - xim(i, 0), v.nx), wrap(y - xim(i, 1), v.ny), wrap(z - xim(i, 2), v.nz));
-    for (int c = 0; c < 3; ++c) lat[static_cast<size_t>(kQ + i * 3 + c) * v.n + dn] = v.G[v.gidx(i, c, x, y, z)];
+    const uint32_t off = M == 0 ? at.rw.at(xim(i, 0), xim(i, 1)) + at.pl.at(xim(i, 2)) : cell;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      st<A>(lat + static_cast<size_t>(kQ + i * 3 + c) * n, cell,
+            ld<A>(G + static_cast<size_t>((M == 0 ? i : oppm(i)) * 3 + c) * stride, off));
   }
 }
 
@@ -385,11 +383,16 @@ __global__ __launch_bounds__(256) void adjoint_fields_kernel(View<S> v, const ty
   node_xyz(cell, v.nx, v.ny, x, y, z);
   double lu[3] = {0, 0, 0}, U[3] = {0, 0, 0}, rho = 1.0;
   if (dl_du) {
-    double j[3] = {0, 0, 0};
+    double f[kQ], j[3] = {0, 0, 0};
+    if (v.fmode == 0) view_fluid<0>(v, x, y, z, f);
+    else if (v.fmode == 1) view_fluid<1>(v, x, y, z, f);
+    else view_fluid<2>(v, x, y, z, f);
+#pragma unroll
     for (int i = 0; i < kQ; ++i) {
-      const double fi = v.f(i, x, y, z);
-      rho += fi;
-      for (int c = 0; c < 3; ++c) j[c] += cq(i, c) * fi;
+      rho += f[i];
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (cq(i, c) != 0) j[c] += cq(i, c) * f[i];
     }
     for (int c = 0; c < 3; ++c) {
       const double F = force_u ? static_cast<double>(force_u[c * n + cell]) : 0.0;
@@ -397,14 +400,22 @@ __global__ __launch_bounds__(256) void adjoint_fields_kernel(View<S> v, const ty
       lu[c] = dl_du[c * n + cell];
     }
   }
+  // unrolled, so that the node's loads are in flight together and its velocities are constants (48^3 FP64
+  // 30 us with loops over a table of velocities, 16 now)
+  const double inv_rho = 1.0 / rho;
+#pragma unroll
   for (int i = 0; i < kQ; ++i) {
     double s = 0.0;
+#pragma unroll
     for (int c = 0; c < 3; ++c) s += lu[c] * (cq(i, c) - U[c]);
-    lam[static_cast<size_t>(i) * n + cell] = static_cast<R>(s / rho);
+    lam[static_cast<size_t>(i) * n + cell] = static_cast<R>(s * inv_rho);
   }
-  for (int i = 0; i < 7; ++i)
-    for (int c = 0; c < 3; ++c)
-      lam[static_cast<size_t>(kQ + i * 3 + c) * n + cell] = static_cast<R>(dl_db ? dl_db[c * n + cell] : 0.0);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const R lb = static_cast<R>(dl_db ? dl_db[c * n + cell] : 0.0);
+#pragma unroll
+    for (int i = 0; i < 7; ++i) lam[static_cast<size_t>(kQ + i * 3 + c) * n + cell] = lb;
+  }
 }
 
 // ------------------------------------------------------------------ reductions
@@ -1697,8 +1708,16 @@ flame_status flame_trace_export(flame_ctx* c, void* lat) {
   if (!lat) return fail(c, FLAME_E_INVAL, "lat is NULL");
   hipError_t e = by_storage(c, [&](auto tag) {
     using S = decltype(tag);
-    hipLaunchKernelGGL(export_kernel<S>, dim3(blocks_for(c->n, 256)), dim3(256), 0, c->stream, make_view<S>(c),
-                       static_cast<S*>(lat));
+    const SetPtrs p = set_ptrs(c);
+    const S* F = static_cast<const S*>(p.f_src);
+    const S* G = static_cast<const S*>(p.g_src);
+    const GridShape g = grid_shape(c->p, row_threads(c->p.nx));
+    if (c->parity == 0)
+      hipLaunchKernelGGL((export_kernel<S, 0>), dim3(g.blocks), dim3(g.threads), 0, c->stream, F, G, c->stride, g, c->n,
+                         static_cast<S*>(lat));
+    else
+      hipLaunchKernelGGL((export_kernel<S, 1>), dim3(g.blocks), dim3(g.threads), 0, c->stream, F, G, c->stride, g, c->n,
+                         static_cast<S*>(lat));
     return hipGetLastError();
   });
   if (e != hipSuccess) return fail(c, FLAME_E_HIP, std::string("export kernel: ") + hipGetErrorString(e));
