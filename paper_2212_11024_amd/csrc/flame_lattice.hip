@@ -63,7 +63,7 @@ struct VStepArgs {
 };
 
 // AA: both sets in place (PAR: even 0 / odd 1); else two-lattice pull for both. Bound by HBM; blocks of
-// consecutive nodes and store hints as in the paper pair's kernel (flame_access.h, flame_step.hip).
+// consecutive nodes as in the paper pair's kernel (flame_access.h), plain stores.
 template <typename S, typename FL, typename ML, bool AA, int PAR, bool BGK, bool EMHD>
 __global__ __launch_bounds__(kRowThreadsMax) void variant_step(VStepArgs<S> a) {
   using E = Enc<S>;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kRowThreadsMax) void variant_step(VStepArgs<S> a) {
   for (int i = 0; i < Q; ++i) {
     const uint32_t off = AA && PAR == 1 ? at.rw.at(FL::c(i, 0), FL::c(i, 1)) + at.pl.at(FL::c(i, 2)) : cell;
     S* base = a.f_dst + static_cast<size_t>(own ? FL::opp(i) : i) * a.stride;
-    st<A, !AA>(base, off, E::enc(f[i], R(fscale<S, FL>(i))));
+    st<A, false>(base, off, E::enc(f[i], R(fscale<S, FL>(i))));
   }
 #pragma unroll
   for (int i = 0; i < ML::m; ++i) {
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kRowThreadsMax) void variant_step(VStepArgs<S> a) {
     const size_t slot = own ? ML::opp(i) : i;
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      st<A, !AA>(a.g_dst + (slot * 3 + c) * a.stride, off, E::enc(g[i * 3 + c], R(fscale<S, ML>(i))));
+      st<A, false>(a.g_dst + (slot * 3 + c) * a.stride, off, E::enc(g[i * 3 + c], R(fscale<S, ML>(i))));
   }
 }
 

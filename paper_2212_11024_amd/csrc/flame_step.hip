@@ -185,7 +185,7 @@ static_assert(kLocalThreads == kRowThreadsMax, "blocks are launched with up to k
 constexpr size_t kFewBlocksNodes = size_t(1) << 25;
 constexpr unsigned kFewBlocksLds = 50000;   // of the 160 KB of a compute unit
 
-template <typename S, bool FAA, bool MAA, int PAR, bool SAVE, int MODEL, Addr A>
+template <typename S, bool FAA, bool MAA, int PAR, bool SAVE, int MODEL, Addr A, bool NT>
 __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
   using R = typename Enc<S>::R;
   uint32_t cell;
@@ -214,13 +214,8 @@ __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
   current_from_moments(lam, Um, B, a.k.alpha, a.k.omega_b, J);
   if (SAVE) save_current<A>(a.save, a.n, cell, J);
   collide_node<MODEL>(f, g, m, U, Um, b, J, F, Sb, a.k);
-  // In place: plain stores, which stay in L2 until the neighbouring wavefronts have filled the
-  // lines that shifted stores share (64^3 FP32 40.5 -> 33 us for two steps, 512^3 FP64 35.8 -> 35.5 ms;
-  // FP32 at 128^3 alone is slower, 318 -> 334 us). Between two lattices the lines are whole and the
-  // non-temporal hint is the better one (161 x 130 x 99 FP32 156 against 161 us a step), as it is
-  // beside a state that is written out (128^3 FP32).
-  store_fluid<S, FAA, PAR, !FAA || SAVE, A>(a, rw, pl, f);
-  store_magnetic<S, MAA, PAR, !MAA || SAVE, A>(a, rw, pl, g);
+  store_fluid<S, FAA, PAR, NT, A>(a, rw, pl, f);
+  store_magnetic<S, MAA, PAR, NT, A>(a, rw, pl, g);
 }
 
 // ------------------------------------------------------------------ stencil-route kernel
@@ -383,12 +378,23 @@ static void launch_local(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>
   // 20.6 ms for two steps, 384^3 9.42 -> 9.33 ms; at 256^3 and below, where it costs 0 to 30%, and in
   // FP16 and FP64, whose registers already bound the blocks, there is no limit).
   const unsigned lds = sizeof(S) == 4 && c->n >= kFewBlocksNodes ? kFewBlocksLds : 0;
-  if (!s.fluid_aa)
-    hipLaunchKernelGGL((step_local<S, false, false, 0, SAVE, MODEL, A>), grid, block, lds, c->stream, a);
-  else if (c->parity == 0)
-    hipLaunchKernelGGL((step_local<S, true, true, 0, SAVE, MODEL, A>), grid, block, lds, c->stream, a);
-  else
-    hipLaunchKernelGGL((step_local<S, true, true, 1, SAVE, MODEL, A>), grid, block, lds, c->stream, a);
+  // Non-temporal stores where what is written cannot be read back from a cache: beside a state that is
+  // written out (128^3 FP32), and between two lattices of more than 384 MB together (161 x 130 x 99 FP32
+  // 156 against 161 us a step, 100^3 FP64 149 against 153). Otherwise plain ones: below that size the
+  // next step finds the lattice in the last-level cache (64^3 FP32 18.5 against 23.5 us, 48^3 FP64 16 against
+  // 20.5), and in place they stay in L2 until the neighbouring wavefronts have filled the lines that
+  // shifted stores share (64^3 FP32 40.5 -> 33 us for two steps, 512^3 FP64 35.8 -> 35.5 ms; FP32 at
+  // 128^3 alone is slower, 318 -> 334 us).
+  if (!s.fluid_aa) {
+    if (SAVE || 2 * 48 * sizeof(S) * c->n > (size_t(384) << 20))
+      hipLaunchKernelGGL((step_local<S, false, false, 0, SAVE, MODEL, A, true>), grid, block, lds, c->stream, a);
+    else
+      hipLaunchKernelGGL((step_local<S, false, false, 0, SAVE, MODEL, A, false>), grid, block, lds, c->stream, a);
+  } else if (c->parity == 0) {
+    hipLaunchKernelGGL((step_local<S, true, true, 0, SAVE, MODEL, A, SAVE>), grid, block, lds, c->stream, a);
+  } else {
+    hipLaunchKernelGGL((step_local<S, true, true, 1, SAVE, MODEL, A, SAVE>), grid, block, lds, c->stream, a);
+  }
 }
 
 template <typename S, bool SAVE, int MODEL>
