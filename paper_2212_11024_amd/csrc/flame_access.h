@@ -29,7 +29,7 @@ struct Rows {
         r[dx + 1][dy + 1] = static_cast<uint32_t>(wrap(y + dy, ny)) * nx + static_cast<uint32_t>(wrap(x + dx, nx));
   }
   // from x and the three row offsets y' * nx
-  __device__ __forceinline__ Rows(uint32_t x, uint32_t nx, uint32_t below, uint32_t row, uint32_t above) {
+  FLAME_HD Rows(uint32_t x, uint32_t nx, uint32_t below, uint32_t row, uint32_t above) {
     const uint32_t xs[3] = {x == 0 ? nx - 1 : x - 1, x, x + 1 == nx ? 0 : x + 1};
     const uint32_t ys[3] = {below, row, above};
 #pragma unroll
@@ -37,7 +37,7 @@ struct Rows {
 #pragma unroll
       for (int dy = 0; dy < 3; ++dy) r[dx][dy] = ys[dy] + xs[dx];
   }
-  __device__ __forceinline__ uint32_t at(int dx, int dy) const { return r[dx + 1][dy + 1]; }
+  FLAME_HD uint32_t at(int dx, int dy) const { return r[dx + 1][dy + 1]; }
 };
 
 // Addressing of the arrays. Every array spans at most 4 GiB (checked by the entry points), so an
@@ -92,13 +92,13 @@ __device__ __forceinline__ void st(S* base, uint32_t off, S v) {
 // Plane offsets of z - 1, z, z + 1 (periodic).
 struct Planes {
   uint32_t p[3];
-  __device__ __forceinline__ Planes(uint32_t below, uint32_t here, uint32_t above) : p{below, here, above} {}
+  FLAME_HD Planes(uint32_t below, uint32_t here, uint32_t above) : p{below, here, above} {}
   __device__ __forceinline__ Planes(int z, int nz, uint32_t plane) {
     p[0] = static_cast<uint32_t>(wrap(z - 1, nz)) * plane;
     p[1] = static_cast<uint32_t>(z) * plane;
     p[2] = static_cast<uint32_t>(wrap(z + 1, nz)) * plane;
   }
-  __device__ __forceinline__ uint32_t at(int dz) const { return p[dz + 1]; }
+  FLAME_HD uint32_t at(int dz) const { return p[dz + 1]; }
 };
 
 // The node-local kernels split the grid by linear node index: a block owns g.threads consecutive
@@ -106,8 +106,8 @@ struct Planes {
 // and a block's own accesses start on a whole cache line also where the rows do not (a row per
 // block leaves 16% of the lanes idle at nx = 161 and straddles a line at both ends of every wavefront).
 // The division by nx and by the plane is a multiplication by floor(2^32 / d), one short at most.
-__device__ __forceinline__ uint32_t div_by(uint32_t t, Divisor d, uint32_t& rest) {
-  uint32_t q = __umulhi(t, d.inv);
+FLAME_HD uint32_t div_by(uint32_t t, Divisor d, uint32_t& rest) {
+  uint32_t q = static_cast<uint32_t>((static_cast<uint64_t>(t) * d.inv) >> 32);
   rest = t - q * d.d;
   if (rest >= d.d) {
     ++q;
@@ -119,7 +119,7 @@ struct NodeAt {
   uint32_t cell;
   Rows rw;
   Planes pl;
-  static __device__ __forceinline__ NodeAt of(uint32_t cell, const GridShape& g) {
+  static FLAME_HD NodeAt of(uint32_t cell, const GridShape& g) {
     uint32_t rem, x;
     const uint32_t z = div_by(cell, g.plane, rem);
     const uint32_t y = div_by(rem, g.nx, x);
