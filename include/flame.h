@@ -42,8 +42,8 @@
  *     multiple of 64 up to 256, larger values taken as 256 (default: the row rounded up to
  *     whole wavefronts, at most 256),
  *     FLAME_GLOBAL_ADDRESSING = 1 makes the node-local step of the paper's velocity sets address
- *     its arrays with 64-bit global addresses (default: buffer resources for FP16 and FP64
- *     storage wherever every array ends at least 16 bytes below 4 GiB).
+ *     its arrays with 64-bit global addresses (default: buffer resources wherever every array
+ *     ends at least 16 bytes below 4 GiB).
  */
 #ifndef FLAME_H
 #define FLAME_H

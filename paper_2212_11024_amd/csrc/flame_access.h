@@ -45,7 +45,7 @@ struct Rows {
 // 64-bit flat-global addresses formed per access in vector registers. Buffer: a buffer resource
 // per array (base in scalar registers, no range limit below 4 GiB, raw addressing) and the 32-bit
 // offset as the only per-lane operand, which takes the 64-bit address arithmetic off the vector
-// ALU (about 140 of the node-local step's 1240 vector instructions per node at FP16 storage).
+// ALU (about 170 of the FP64 in-place odd step's 880 vector instructions per node).
 enum class Addr { Global, Buffer };
 typedef unsigned int U32x2 __attribute__((ext_vector_type(2)));
 template <typename S>

@@ -13,9 +13,9 @@
 //
 // Two kernels:
 //   step_local  - moment-route J: every node independent, one node per thread, blocks of up to
-//     256 consecutive nodes; with FP16 and FP64 storage its arrays are addressed through buffer
-//     resources when every array ends at least 16 bytes below 4 GiB, otherwise (and with FP32
-//     storage) through 64-bit global addresses (bitwise the same step either way).
+//     256 consecutive nodes; its arrays are addressed through buffer resources when every array
+//     ends at least 16 bytes below 4 GiB, otherwise through 64-bit global addresses (bitwise the
+//     same step either way).
 //   step_zmarch - stencil J: a workgroup owns a 64 x 8 tile of (x, y) and marches along z. It
 //     keeps the field fluctuation b of three consecutive planes in LDS (computed once per node
 //     from that node's own magnetic populations, which it holds in registers for the next
@@ -410,15 +410,13 @@ static void launch_model(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>
     else
       hipLaunchKernelGGL((step_zmarch<S, true, 1, SAVE, MODEL>), grid, block, 0, c->stream, a);
   } else {
-    // FP16 and FP64 storage: buffer resources (timed on the same buffers at 512^3, FP16 6.05-6.12
-    // against 6.43-6.50 ms, FP64 18.91-19.13 against 19.17-19.30 ms); FP32 keeps the global
-    // addresses, with which it runs 1.1-2.5% faster (9.09 against 9.20 ms on a fast placement)
-    if constexpr (sizeof(S) != 4) {
-      const bool arith_arrays = SAVE || c->p.force_u || c->p.force_b;
-      if (!c->global_addr && buffer_addressing_ok(c->p, arith_arrays)) {
-        launch_local<S, SAVE, MODEL, Addr::Buffer>(c, s, a);
-        return;
-      }
+    // Buffer resources wherever the arrays fit: about 100 vector instructions of address arithmetic less
+    // (two steps on the same buffers: FP32 256^3 2.75 against 2.78 ms, 161 x 130 x 99 322 against 328 us, 64^3 AB
+    // 35.7 against 36.2 us, 320^3 alone 5.16 against 5.12 ms).
+    const bool arith_arrays = SAVE || c->p.force_u || c->p.force_b;
+    if (!c->global_addr && buffer_addressing_ok(c->p, arith_arrays)) {
+      launch_local<S, SAVE, MODEL, Addr::Buffer>(c, s, a);
+      return;
     }
     launch_local<S, SAVE, MODEL, Addr::Global>(c, s, a);
   }
