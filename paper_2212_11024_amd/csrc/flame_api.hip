@@ -1449,10 +1449,26 @@ bool make_plan(flame_ctx* c, hipfftHandle& plan, bool& ok, hipfftType type) {
   return hipfftSetStream(plan, c->stream) == HIPFFT_SUCCESS;
 }
 
+// The plans that a call needs, for spec_batch components; where a batch of three cannot be planned
+// (no memory for the work area that some lengths need), for one.
+bool spectral_plans(flame_ctx* c, bool inverse) {
+  for (;;) {
+    if (make_plan(c, c->plan, c->plan_ok, HIPFFT_D2Z) &&
+        (!inverse || make_plan(c, c->plan_inv, c->plan_inv_ok, HIPFFT_Z2D)))
+      return true;
+    if (c->spec_batch == 1) return false;
+    if (c->plan_ok) hipfftDestroy(c->plan);
+    if (c->plan_inv_ok) hipfftDestroy(c->plan_inv);
+    c->plan_ok = c->plan_inv_ok = false;
+    c->spec_batch = 1;
+    (void)hipGetLastError();  // clear an allocation error so later launch checks do not see it
+  }
+}
+
 // Workspace of the in-place transforms: three components at once (one batched transform, one pass over
 // the populations; 64^3 22 us against 3 x 12, from 256^3 on as fast as three), or one where the memory
 // for three is not there or an array spans too many values for the batch.
-flame_status spectral_setup(flame_ctx* c, int blocks, int terms, int nshells) {
+flame_status spectral_setup(flame_ctx* c, int blocks, int terms, int nshells, bool inverse) {
   const size_t nh = half_shape(c).nh;
   if (!c->spec_work) {
     c->spec_batch = 2 * nh <= 0x7fffffff ? 3 : 1;
@@ -1461,7 +1477,7 @@ flame_status spectral_setup(flame_ctx* c, int blocks, int terms, int nshells) {
       if (!keep_at_least(c->spec_work, c->spec_work_size, nh)) return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
     }
   }
-  if (!make_plan(c, c->plan, c->plan_ok, HIPFFT_D2Z)) return fail(c, FLAME_E_HIP, "forward transform plan failed");
+  if (!spectral_plans(c, inverse)) return fail(c, FLAME_E_HIP, "transform plan failed");
   // block partials plus one row for their merged sums, per term
   if (!keep_at_least(c->spec_partials, c->spec_partials_size, static_cast<size_t>(terms) * (blocks + 1) * nshells))
     return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
@@ -1494,7 +1510,7 @@ flame_status shell_spectrum(flame_ctx* c, int32_t field, int32_t nshells, int k2
   if (!e_k) return fail(c, FLAME_E_INVAL, "e_k is NULL");
   const HalfShape h = half_shape(c);
   const int blocks = bin_blocks(h, nshells);
-  const flame_status ready = spectral_setup(c, blocks, 1, nshells);
+  const flame_status ready = spectral_setup(c, blocks, 1, nshells, false);
   if (ready != FLAME_OK) return ready;
   for (int s = 0; s < nshells; ++s) e_k[s] = 0.0;
   const double norm2 = 1.0 / (static_cast<double>(c->n) * static_cast<double>(c->n));
@@ -1565,9 +1581,8 @@ flame_status energy_transfer(flame_ctx* c, int32_t nshells, double* t_adv, doubl
   const uint32_t pitch = 2 * static_cast<uint32_t>(h.nxh);
   const size_t nh = h.nh, dist = 2 * nh;
   const int blocks = bin_blocks(h, nshells), terms = t_hall ? 4 : 3;
-  const flame_status ready = spectral_setup(c, blocks, terms, nshells);
+  const flame_status ready = spectral_setup(c, blocks, terms, nshells, true);
   if (ready != FLAME_OK) return ready;
-  if (!make_plan(c, c->plan_inv, c->plan_inv_ok, HIPFFT_Z2D)) return fail(c, FLAME_E_HIP, "inverse transform plan failed");
   const int nb = c->spec_batch;
   TransferRelease release{c};
   // u_hat(3), B_hat(3), then the real fields U(3), B(3), J(3) (in units of a complex value)
