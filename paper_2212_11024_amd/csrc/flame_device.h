@@ -467,17 +467,22 @@ FLAME_HD void collide_magnetic(R (&g)[kM], const R (&U)[3], const R (&B)[3],
 template <typename R>
 FLAME_HD void collide_fluid_bgk(R (&f)[kQ], const FluidMoments<R>& m, const R (&U)[3], const R (&b)[3],
                                 const R (&b0)[3], const R (&F)[3], R omega) {
-  // With T = f^mhd(0) + (1/w - 1/2) sum_a F_a H^a this is f* = T + (1 - w)(f - T).
-  const R om1 = R(1) - omega;
-  const R fk = (R(1) - R(0.5) * omega) / omega;
+  // With T = f^mhd(0) + (1/w - 1/2) sum_a F_a H^a this is f* = T + (1 - w)(f - T), which keeps a
+  // small f - T exact. Below w = 1 the force in T outgrows f, so there the form is f* = w T + (1 - w) f
+  // (both terms positive weights of f), with the factor w taken into the coefficients.
+  const bool slow = omega < R(1);
+  const R om1 = R(1) - omega, s = slow ? omega : R(1), keep = slow ? R(0) : R(1);
+  const R fk = (R(1) - R(0.5) * omega) / (slow ? R(1) : omega);   // w may be 0 in FP32
   R a[kQ], M[6];
-  central_coefficients(R(1) + m.drho, {R(0), R(0), R(0), R(0), R(0), R(0)}, {fk * F[0], fk * F[1], fk * F[2]}, a);
+  central_coefficients(s * (R(1) + m.drho), {R(0), R(0), R(0), R(0), R(0), R(0)}, {fk * F[0], fk * F[1], fk * F[2]}, a);
   maxwell_change(b, b0, M);
-  populate(a, m.drho, U, M);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) M[k] *= s;
+  populate(a, s * m.drho, U, M);
 #pragma unroll
   for (int i = 0; i < kQ; ++i) {
     const R t = a[tidx(cq(i, 0) + 1, cq(i, 1) + 1, cq(i, 2) + 1)];
-    f[i] = t + om1 * (f[i] - t);
+    f[i] = t + om1 * (f[i] - keep * t);
   }
 }
 
