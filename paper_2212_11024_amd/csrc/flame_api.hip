@@ -391,8 +391,7 @@ __global__ __launch_bounds__(256) void adjoint_fields_kernel(View<S> v, const ty
     for (int i = 0; i < kQ; ++i) {
       rho += f[i];
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (cq(i, c) != 0) j[c] += cq(i, c) * f[i];
+      for (int c = 0; c < 3; ++c) j[c] += cq(i, c) * f[i];   // also where c is 0: an infinity makes U NaN
     }
     for (int c = 0; c < 3; ++c) {
       const double F = force_u ? static_cast<double>(force_u[c * n + cell]) : 0.0;
@@ -573,8 +572,7 @@ __global__ __launch_bounds__(kRedThreads) void stencil_march_kernel(AuxArgs<S> a
           fin = fin && isfinite(f);
           drho += f;
 #pragma unroll
-          for (int c = 0; c < 3; ++c)
-            if (cq(i, c) != 0) j[c] += cq(i, c) * f;
+          for (int c = 0; c < 3; ++c) j[c] += cq(i, c) * f;   // also where c is 0, as in node_quantities
         }
         q.rho = 1.0 + drho;
         q.finite = fin;
@@ -693,8 +691,7 @@ __global__ __launch_bounds__(256) void field_kernel(AuxArgs<S> a, GridShape shap
     for (int i = 0; i < kQ; ++i) {
       drho += f[i];
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (cq(i, c) != 0) j[c] += cq(i, c) * f[i];
+      for (int c = 0; c < 3; ++c) j[c] += cq(i, c) * f[i];   // also where c is 0, as in node_quantities
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
