@@ -40,11 +40,13 @@ def spectral_gradient(v: torch.Tensor) -> torch.Tensor:
             f[n // 2] = 0.0           # the Nyquist mode has no well-defined derivative
         return f
 
-    # real transforms (half the spectrum), the three axes back in one batch: with complex ones and one
-    # inverse per axis the gradients took 0.8 ms of a 2.1 ms rollout of 12 steps at 48^3
+    # real transforms (half the spectrum), one axis at a time: complex ones took 0.26 ms at 48^3 and 8.7 ms at
+    # 256^3 (these 0.21 and 5.3) and 290 to 360 bytes a node of memory at the peak (these 170); all nine
+    # derivatives in one batch take 0.18 and 5.3 ms, but 320 bytes and 0.14 ms more with the backward at 48^3.
+    # The stack makes the result dense, whatever the strides that a transform returns.
     vh = torch.fft.rfftn(v, dim=(1, 2, 3))
     ik = (k(nx, torch.fft.rfftfreq).view(1, 1, -1), k(ny).view(1, ny, 1), k(nz).view(nz, 1, 1))
-    return torch.fft.irfftn(torch.stack([1j * ka * vh for ka in ik]), s=(nz, ny, nx), dim=(2, 3, 4))
+    return torch.stack([torch.fft.irfftn(1j * ka * vh, s=(nz, ny, nx), dim=(1, 2, 3)) for ka in ik])
 
 
 def shell_spectrum(v: torch.Tensor, nshells: int) -> torch.Tensor:
@@ -117,7 +119,10 @@ class FlameRollout(torch.autograd.Function):
         _, u, B, _, _ = s.fields()
         ctx.solver, ctx.ckpts, ctx.cfg = s, ckpts, cfg
         ctx.has_grads = (gu0 is not None, gb0 is not None)
-        ctx.save_for_backward(u0.detach(), b0.detach(), *(t.detach() for t in (gu0, gb0) if t is not None))
+        given = [t for t in (u0, b0, gu0, gb0) if t is not None]
+        ctx.given_as = [(t.device, t.dtype) for t in given]
+        # as the library reads them, by pointer: dense float64 on the run's device, as the run itself was given them
+        ctx.save_for_backward(*(t.detach().to(s.device, torch.float64).contiguous() for t in given))
         return u.clone(), B.clone()
 
     @staticmethod
@@ -167,7 +172,9 @@ class FlameRollout(torch.autograd.Function):
         L.flame_adjoint_init(s.ctx, lam.data_ptr(), u0.data_ptr(), b0.data_ptr(), ptr(gu0), ptr(gb0),
                              out_u.data_ptr(), out_b.data_ptr(), ptr(out_gu), ptr(out_gb))
         s.stream.synchronize()
-        return out_u, out_b, out_gu, out_gb, None
+        grads = iter([g.to(*like) for g, like in zip([g for g in (out_u, out_b, out_gu, out_gb) if g is not None],
+                                                     ctx.given_as)])
+        return next(grads), next(grads), None if gu0 is None else next(grads), None if gb0 is None else next(grads), None
 
 
 def rollout(u0, b0, cfg: RolloutConfig, noneq: bool = True):
