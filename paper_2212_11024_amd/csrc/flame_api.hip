@@ -751,6 +751,20 @@ __device__ __forceinline__ BinEntry bin_entry(uint32_t t, const HalfShape& h) {
   return e;
 }
 
+// Orders LDS accesses between the lanes of a binning block, which is one wavefront: a lane's add follows the
+// clearing and the adds of other lanes to the same bin. (No instruction: the hardware keeps the order of one
+// wavefront's LDS operations.)
+static_assert(kBinThreads == 64, "a binning block is one wavefront");
+__device__ __forceinline__ void bins_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ void bins_clear(double* bins, int count) {
+  for (int s = threadIdx.x; s < count; s += kBinThreads) bins[s] = 0.0;
+  bins_sync();
+}
+
 // Add v of every lane to bins[shell]; called by all 64 lanes together.
 __device__ __forceinline__ void bin_piece(double* bins, int nshells, int shell, double v) {
   const int lane = threadIdx.x;
@@ -762,6 +776,7 @@ __device__ __forceinline__ void bin_piece(double* bins, int nshells, int shell, 
   }
   const int next = __shfl_down(shell, 1, kBinThreads);
   if ((lane == kBinThreads - 1 || next != shell) && shell >= 0 && shell < nshells) bins[shell] += v;
+  bins_sync();
 }
 
 // Block partials of the bins, one row of nshells per block; added to what is there unless first.
@@ -780,7 +795,7 @@ __global__ __launch_bounds__(kBinThreads) void shell_bin_kernel(const hipfftDoub
                                                                 int nshells, double norm2, int k2, int first,
                                                                 double* partials) {
   extern __shared__ double bins[];
-  for (int s = threadIdx.x; s < nshells; s += kBinThreads) bins[s] = 0.0;
+  bins_clear(bins, nshells);
   for (uint32_t t = blockIdx.x; t < h.total; t += gridDim.x) {
     const BinEntry e = bin_entry(t, h);
     double v = 0.0;
@@ -905,7 +920,7 @@ __global__ __launch_bounds__(kBinThreads) void transfer_bin_kernel(const hipfftD
                                                                    double norm2, double* partials, double* ipartials) {
   extern __shared__ double bins[];
   double* ibins = bins + (X ? nshells : 0);
-  for (int s = threadIdx.x; s < (X ? nshells : 0) + (Bh ? nshells : 0); s += kBinThreads) bins[s] = 0.0;
+  bins_clear(bins, (X ? nshells : 0) + (Bh ? nshells : 0));
   for (uint32_t t = blockIdx.x; t < h.total; t += gridDim.x) {
     const BinEntry e = bin_entry(t, h);
     double v = 0.0, w = 0.0;
