@@ -1454,46 +1454,49 @@ bool make_plan(flame_ctx* c, hipfftHandle& plan, bool& ok, hipfftType type) {
   const bool many = c->spec_batch > 1;     // the distances only count then, and fit in an int (spectral_setup)
   const int dist = many ? static_cast<int>(half_shape(c).nh) : 1, rdist = many ? 2 * dist : 1;
   const bool fwd = type == HIPFFT_D2Z;
-  if (hipfftPlanMany(&plan, 3, n, fwd ? real : half, 1, fwd ? rdist : dist, fwd ? half : real, 1, fwd ? dist : rdist, type,
-                     c->spec_batch) != HIPFFT_SUCCESS)
-    return false;
-  ok = true;
-  return hipfftSetStream(plan, c->stream) == HIPFFT_SUCCESS;
+  size_t work = 0;
+  if (hipfftCreate(&plan) != HIPFFT_SUCCESS) return false;
+  // a plan counts as made only once it runs on the context's stream
+  ok = hipfftMakePlanMany(plan, 3, n, fwd ? real : half, 1, fwd ? rdist : dist, fwd ? half : real, 1, fwd ? dist : rdist,
+                          type, c->spec_batch, &work) == HIPFFT_SUCCESS &&
+       hipfftSetStream(plan, c->stream) == HIPFFT_SUCCESS;
+  if (!ok) hipfftDestroy(plan);
+  return ok;
 }
 
-// The plans that a call needs, for spec_batch components; where a batch of three cannot be planned
-// (no memory for the work area that some lengths need), for one.
-bool spectral_plans(flame_ctx* c, bool inverse) {
-  for (;;) {
-    if (make_plan(c, c->plan, c->plan_ok, HIPFFT_D2Z) &&
-        (!inverse || make_plan(c, c->plan_inv, c->plan_inv_ok, HIPFFT_Z2D)))
-      return true;
-    if (c->spec_batch == 1) return false;
-    if (c->plan_ok) hipfftDestroy(c->plan);
-    if (c->plan_inv_ok) hipfftDestroy(c->plan_inv);
-    c->plan_ok = c->plan_inv_ok = false;
-    c->spec_batch = 1;
-    (void)hipGetLastError();  // clear an allocation error so later launch checks do not see it
-  }
+// Release what the transforms of three components hold and go on with one.
+void one_component(flame_ctx* c) {
+  if (c->plan_ok) hipfftDestroy(c->plan);
+  if (c->plan_inv_ok) hipfftDestroy(c->plan_inv);
+  c->plan_ok = c->plan_inv_ok = false;
+  if (c->spec_work) (void)hipFree(c->spec_work);
+  c->spec_work = nullptr;
+  c->spec_work_size = 0;
+  c->spec_batch = 1;
+  (void)hipGetLastError();  // clear an allocation error so later launch checks do not see it
 }
 
 // Workspace of the in-place transforms: three components at once (one batched transform, one pass over
-// the populations; 64^3 22 us against 3 x 12, from 256^3 on as fast as three), or one where the memory
-// for three is not there or an array spans too many values for the batch.
-flame_status spectral_setup(flame_ctx* c, int blocks, int terms, int nshells, bool inverse) {
+// the populations; 64^3 22 us against 3 x 12, from 256^3 on as fast as three), or one where an array spans
+// too many values for the batch or where the memory for three (with the transfer values of
+// transfer_work that the call needs, and the work areas of the plans) is not there.
+flame_status spectral_setup(flame_ctx* c, int blocks, int terms, int nshells, bool inverse, size_t transfer) {
   const size_t nh = half_shape(c).nh;
-  if (!c->spec_work) {
-    c->spec_batch = 2 * nh <= 0x7fffffff ? 3 : 1;
-    if (!keep_at_least(c->spec_work, c->spec_work_size, c->spec_batch * nh)) {
-      c->spec_batch = 1;
-      if (!keep_at_least(c->spec_work, c->spec_work_size, nh)) return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
-    }
+  if (c->spec_batch == 0) c->spec_batch = 2 * nh <= 0x7fffffff ? 3 : 1;
+  for (;;) {
+    // block partials plus one row for their merged sums, per term
+    const bool memory =
+        keep_at_least(c->spec_work, c->spec_work_size, c->spec_batch * nh) &&
+        keep_at_least(c->spec_partials, c->spec_partials_size, static_cast<size_t>(terms) * (blocks + 1) * nshells) &&
+        (transfer == 0 || keep_at_least(c->transfer_work, c->transfer_size, transfer));
+    if (memory && make_plan(c, c->plan, c->plan_ok, HIPFFT_D2Z) &&
+        (!inverse || make_plan(c, c->plan_inv, c->plan_inv_ok, HIPFFT_Z2D)))
+      return FLAME_OK;
+    if (c->spec_batch == 1)
+      return memory ? fail(c, FLAME_E_HIP, "transform plan failed")
+                    : fail(c, FLAME_E_NOMEM, transfer ? "energy transfer: device workspace" : "spectrum: device workspace");
+    one_component(c);
   }
-  if (!spectral_plans(c, inverse)) return fail(c, FLAME_E_HIP, "transform plan failed");
-  // block partials plus one row for their merged sums, per term
-  if (!keep_at_least(c->spec_partials, c->spec_partials_size, static_cast<size_t>(terms) * (blocks + 1) * nshells))
-    return fail(c, FLAME_E_NOMEM, "spectrum: device workspace");
-  return FLAME_OK;
 }
 
 // Fewer blocks for many shells: the block partials stay within 64 MiB a term.
@@ -1522,7 +1525,7 @@ flame_status shell_spectrum(flame_ctx* c, int32_t field, int32_t nshells, int k2
   if (!e_k) return fail(c, FLAME_E_INVAL, "e_k is NULL");
   const HalfShape h = half_shape(c);
   const int blocks = bin_blocks(h, nshells);
-  const flame_status ready = spectral_setup(c, blocks, 1, nshells, false);
+  const flame_status ready = spectral_setup(c, blocks, 1, nshells, false, 0);
   if (ready != FLAME_OK) return ready;
   for (int s = 0; s < nshells; ++s) e_k[s] = 0.0;
   const double norm2 = 1.0 / (static_cast<double>(c->n) * static_cast<double>(c->n));
@@ -1593,14 +1596,13 @@ flame_status energy_transfer(flame_ctx* c, int32_t nshells, double* t_adv, doubl
   const uint32_t pitch = 2 * static_cast<uint32_t>(h.nxh);
   const size_t nh = h.nh, dist = 2 * nh;
   const int blocks = bin_blocks(h, nshells), terms = t_hall ? 4 : 3;
-  const flame_status ready = spectral_setup(c, blocks, terms, nshells, true);
-  if (ready != FLAME_OK) return ready;
-  const int nb = c->spec_batch;
-  TransferRelease release{c};
   // u_hat(3), B_hat(3), then the real fields U(3), B(3), J(3) (in units of a complex value)
   const size_t field3 = (3 * n + 1) / 2;
-  if (!keep_at_least(c->transfer_work, c->transfer_size, 6 * nh + std::max(3 * field3, field3 + 3 * nh)))
-    return fail(c, FLAME_E_NOMEM, "energy transfer: device workspace");
+  TransferRelease release{c};
+  const flame_status ready =
+      spectral_setup(c, blocks, terms, nshells, true, 6 * nh + std::max(3 * field3, field3 + 3 * nh));
+  if (ready != FLAME_OK) return ready;
+  const int nb = c->spec_batch;
   hipfftDoubleComplex* Uh = c->transfer_work;
   hipfftDoubleComplex* Bh = Uh + 3 * nh;
   hipfftDoubleComplex* base = Uh + 6 * nh;
