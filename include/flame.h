@@ -220,9 +220,13 @@ flame_status flame_reduce_noalloc(flame_ctx* c, double* out);
 /* Shell energy spectrum of u (field = 0) or B (field = 1) into host e_k[nshells]:
  * E(s) = 1/2 sum_{round(|k|) = s} |v_hat(k)|^2, v_hat = DFT(v) / ncell, k the signed integer
  * wavevector (paper Sec. 4.4 spectra). FP64 FFT (hipFFT) and binning in a fixed order (no
- * atomics), so the spectrum of a given state is bitwise reproducible. Synchronises. The first
- * call allocates a workspace of one node field and one half spectrum (kept until flame_destroy);
- * FLAME_E_NOMEM if that fails, and a later call tries again. */
+ * atomics), so the spectrum of a given state is bitwise reproducible as long as the workspace holds as
+ * many components. Synchronises. Device memory, allocated by the first call that needs it and kept until
+ * flame_destroy (FLAME_E_NOMEM if that fails, and a later call tries again): three half spectra, 24
+ * bytes a node, with the work area of their transform where both take at most 4 GiB, else, or where there
+ * is no memory for them, one half spectrum with its work area; and up to 64 MiB of partial sums for
+ * each term. The work area is empty or as large as the half spectra for most grids (none at 512^3, as large
+ * at 560^3) and up to four times as large where a grid size has a prime factor above 7. */
 flame_status flame_spectrum(flame_ctx* c, int32_t field, int32_t nshells, double* e_k);
 
 /* Shell dissipation spectrum of u (field = 0) or B (field = 1) into host d_k[nshells]:
@@ -249,8 +253,10 @@ flame_status flame_dissipation_spectrum(flame_ctx* c, int32_t field, int32_t nsh
  * Hall term, -sum_{s < k} t_hall is added to the right-hand side).
  * Derivatives are spectral, q_a = 2 pi k_a / n_a, and 0 on the Nyquist index of an even axis;
  * products are formed node by node. FP64 throughout (hipFFT), shell sums in a fixed order
- * (bitwise reproducible for a given state). Allocates 11 node fields and 7
- * half spectra of device memory for the call (19 GB at 512^3) and frees them before returning;
+ * (bitwise reproducible for a given state, as flame_spectrum). Device memory: the workspace of
+ * flame_spectrum, with an inverse plan and partial sums for 4 terms, kept until flame_destroy, and 6
+ * half spectra and 9 node fields (120 bytes a node, 16 GB at 512^3), which are kept until
+ * flame_destroy where they take at most 4 GiB (about 330^3) and else freed before the call returns;
  * FLAME_E_NOMEM if that fails. FLAME_E_INVAL for nshells outside 1..4096 or a NULL t_adv, t_lor
  * or t_ind. Synchronises. */
 flame_status flame_energy_transfer(flame_ctx* c, int32_t nshells, double* t_adv, double* t_lor, double* t_ind,

@@ -1446,18 +1446,23 @@ bool keep_at_least(T*& ptr, size_t& have, size_t count) {
   return true;
 }
 
-bool make_plan(flame_ctx* c, hipfftHandle& plan, bool& ok, hipfftType type) {
+// Device memory that a context keeps between calls for the fields of a diagnostic: what is larger goes by
+// one component at a time (the transforms) or is released at the end of the call (the energy transfer).
+constexpr size_t kKeepBytes = size_t(4) << 30;
+
+// A plan without a work area of its own; work returns the bytes that it needs.
+bool make_plan(flame_ctx* c, hipfftHandle& plan, bool& ok, hipfftType type, size_t& work) {
   if (ok) return true;
   int n[3] = {c->p.nz, c->p.ny, c->p.nx};
   const int nxh = c->p.nx / 2 + 1;
   int real[3] = {c->p.nz, c->p.ny, 2 * nxh}, half[3] = {c->p.nz, c->p.ny, nxh};
-  const bool many = c->spec_batch > 1;     // the distances only count then, and fit in an int (spectral_setup)
+  const bool many = c->spec_batch > 1;     // the distances only count then, and fit in an int (kKeepBytes)
   const int dist = many ? static_cast<int>(half_shape(c).nh) : 1, rdist = many ? 2 * dist : 1;
   const bool fwd = type == HIPFFT_D2Z;
-  size_t work = 0;
   if (hipfftCreate(&plan) != HIPFFT_SUCCESS) return false;
   // a plan counts as made only once it runs on the context's stream
-  ok = hipfftMakePlanMany(plan, 3, n, fwd ? real : half, 1, fwd ? rdist : dist, fwd ? half : real, 1, fwd ? dist : rdist,
+  ok = hipfftSetAutoAllocation(plan, 0) == HIPFFT_SUCCESS &&
+       hipfftMakePlanMany(plan, 3, n, fwd ? real : half, 1, fwd ? rdist : dist, fwd ? half : real, 1, fwd ? dist : rdist,
                           type, c->spec_batch, &work) == HIPFFT_SUCCESS &&
        hipfftSetStream(plan, c->stream) == HIPFFT_SUCCESS;
   if (!ok) hipfftDestroy(plan);
@@ -1469,32 +1474,42 @@ void one_component(flame_ctx* c) {
   if (c->plan_ok) hipfftDestroy(c->plan);
   if (c->plan_inv_ok) hipfftDestroy(c->plan_inv);
   c->plan_ok = c->plan_inv_ok = false;
+  c->plan_work = c->plan_inv_work = 0;
   if (c->spec_work) (void)hipFree(c->spec_work);
+  if (c->fft_work) (void)hipFree(c->fft_work);
   c->spec_work = nullptr;
-  c->spec_work_size = 0;
+  c->fft_work = nullptr;
+  c->spec_work_size = c->fft_work_size = 0;
   c->spec_batch = 1;
   (void)hipGetLastError();  // clear an allocation error so later launch checks do not see it
 }
 
 // Workspace of the in-place transforms: three components at once (one batched transform, one pass over
-// the populations; 64^3 22 us against 3 x 12, from 256^3 on as fast as three), or one where an array spans
-// too many values for the batch or where the memory for three (with the transfer values of
-// transfer_work that the call needs, and the work areas of the plans) is not there.
+// the populations; 64^3 22 us against 3 x 12, from 256^3 on as fast as three), or one where three with the
+// plans' work area (none, or one to four times as much again, by the prime factors and the size of the
+// grid) are more than is kept, or where the memory for three (with the transfer values of transfer_work
+// that the call needs) is not there.
 flame_status spectral_setup(flame_ctx* c, int blocks, int terms, int nshells, bool inverse, size_t transfer) {
   const size_t nh = half_shape(c).nh;
-  if (c->spec_batch == 0) c->spec_batch = 2 * nh <= 0x7fffffff ? 3 : 1;
+  if (c->spec_batch == 0) c->spec_batch = 3 * nh * sizeof(hipfftDoubleComplex) <= kKeepBytes ? 3 : 1;
   for (;;) {
+    const bool planned = make_plan(c, c->plan, c->plan_ok, HIPFFT_D2Z, c->plan_work) &&
+                         (!inverse || make_plan(c, c->plan_inv, c->plan_inv_ok, HIPFFT_Z2D, c->plan_inv_work));
+    const size_t work = std::max(c->plan_work, c->plan_inv_work);
+    const bool kept = c->spec_batch == 1 || 3 * nh * sizeof(hipfftDoubleComplex) + work <= kKeepBytes;
     // block partials plus one row for their merged sums, per term
     const bool memory =
-        keep_at_least(c->spec_work, c->spec_work_size, c->spec_batch * nh) &&
+        planned && kept && keep_at_least(c->spec_work, c->spec_work_size, c->spec_batch * nh) &&
+        (work == 0 || keep_at_least(c->fft_work, c->fft_work_size, work)) &&
         keep_at_least(c->spec_partials, c->spec_partials_size, static_cast<size_t>(terms) * (blocks + 1) * nshells) &&
         (transfer == 0 || keep_at_least(c->transfer_work, c->transfer_size, transfer));
-    if (memory && make_plan(c, c->plan, c->plan_ok, HIPFFT_D2Z) &&
-        (!inverse || make_plan(c, c->plan_inv, c->plan_inv_ok, HIPFFT_Z2D)))
+    if (memory && (work == 0 || (hipfftSetWorkArea(c->plan, c->fft_work) == HIPFFT_SUCCESS &&
+                                 (!c->plan_inv_ok || hipfftSetWorkArea(c->plan_inv, c->fft_work) == HIPFFT_SUCCESS))))
       return FLAME_OK;
     if (c->spec_batch == 1)
-      return memory ? fail(c, FLAME_E_HIP, "transform plan failed")
-                    : fail(c, FLAME_E_NOMEM, transfer ? "energy transfer: device workspace" : "spectrum: device workspace");
+      return !planned || memory
+                 ? fail(c, FLAME_E_HIP, "transform plan failed")
+                 : fail(c, FLAME_E_NOMEM, transfer ? "energy transfer: device workspace" : "spectrum: device workspace");
     one_component(c);
   }
 }
@@ -1571,13 +1586,13 @@ flame_status flame_dissipation_spectrum(flame_ctx* c, int32_t field, int32_t nsh
 
 namespace {
 
-// Node fields and transforms of the energy transfer, kept by the context up to this size (300^3) and
-// else released at the end of the call: allocating and freeing them took 30 ms of a 37 ms call at 192^3.
-constexpr size_t kTransferKeepBytes = size_t(4) << 30;
+// Node fields and transforms of the energy transfer (120 bytes a node), kept by the context up to
+// kKeepBytes (330^3) and else released at the end of the call: allocating and freeing them took 30 ms of a
+// 37 ms call at 192^3.
 struct TransferRelease {
   flame_ctx* c;
   ~TransferRelease() {
-    if (!c->transfer_work || c->transfer_size * sizeof(hipfftDoubleComplex) <= kTransferKeepBytes) return;
+    if (!c->transfer_work || c->transfer_size * sizeof(hipfftDoubleComplex) <= kKeepBytes) return;
     (void)hipStreamSynchronize(c->stream);   // work queued on an error path may still use it
     (void)hipFree(c->transfer_work);
     c->transfer_work = nullptr;
@@ -1781,6 +1796,7 @@ void flame_destroy(flame_ctx* c) {
   if (c->plan_ok) hipfftDestroy(c->plan);
   if (c->plan_inv_ok) hipfftDestroy(c->plan_inv);
   if (c->red_partials) (void)hipFree(c->red_partials);
+  if (c->fft_work) (void)hipFree(c->fft_work);
   if (c->spec_work) (void)hipFree(c->spec_work);
   if (c->transfer_work) (void)hipFree(c->transfer_work);
   if (c->spec_partials) (void)hipFree(c->spec_partials);

@@ -42,6 +42,9 @@ struct flame_ctx {
   size_t spec_partials_size = 0;
   hipfftDoubleComplex* transfer_work = nullptr;   // fields and transforms of the energy transfer
   size_t transfer_size = 0;
+  char* fft_work = nullptr;                   // work area of both plans, which run one after the other
+  size_t fft_work_size = 0;
+  size_t plan_work = 0, plan_inv_work = 0;    // bytes of it that each plan needs
   hipfftHandle plan{};
   bool plan_ok = false;
   hipfftHandle plan_inv{};   // complex-to-real inverse, for spectral derivatives

@@ -91,3 +91,16 @@ def test_a_plan_without_the_stream_is_not_used(ss, failures):
     assert ss.ss_setup(c, SHELLS, 0) == L.FLAME_OK
     assert ss.ss_plans() == 1
     _ok(ss, c, 1)
+
+
+@pytest.mark.parametrize("n,work_factor,batch", [(256, 0.0, 3), (512, 0.0, 3), (512, 1.0, 1), (420, 1.0, 3), (300, 4.0, 3),
+                                                 (331, 4.0, 1), (576, 0.0, 1)])
+def test_three_components_are_kept_up_to_4_gib_with_their_work_area(ss, n, work_factor, batch):
+    c = ss.ss_new(n, n, n, 64 * GIB, work_factor)
+    half = 16 * (n // 2 + 1) * n * n
+    for transfer in (0, 6 * half + 72 * n ** 3):
+        assert ss.ss_setup(c, SHELLS, transfer) == L.FLAME_OK
+        _ok(ss, c, batch)
+        spectra = batch * half * (1 + work_factor)       # one work area for both plans
+        assert batch == 1 or spectra <= 4 * GIB
+        assert abs(ss.ss_held() - spectra - transfer) < 8 << 20
