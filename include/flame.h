@@ -44,6 +44,9 @@
  *     FLAME_GLOBAL_ADDRESSING = 1 makes the node-local step of the paper's velocity sets address
  *     its arrays with 64-bit global addresses (default: buffer resources wherever every array
  *     ends at least 16 bytes below 4 GiB).
+ *   - FLAME_SPECTRAL_BATCH = 1, read by flame_init too, makes the spectra and the energy transfer work
+ *     on one component at a time with a third of the memory, as they do where there is none for three
+ *     (see flame_spectrum; results agree to rounding).
  */
 #ifndef FLAME_H
 #define FLAME_H

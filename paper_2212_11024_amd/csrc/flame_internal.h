@@ -37,7 +37,7 @@ struct flame_ctx {
   double* scratch = nullptr;   // this device's static reduction scratch (not owned)
   hipfftDoubleComplex* spec_work = nullptr;   // spec_batch components, transformed in place
   size_t spec_work_size = 0;
-  int spec_batch = 0;                         // components per transform (3, or 1 for want of memory)
+  int spec_batch = 0;                         // components per transform: 3 or 1 (0: not decided yet)
   double* spec_partials = nullptr;            // block partials and merged rows of the shell sums
   size_t spec_partials_size = 0;
   hipfftDoubleComplex* transfer_work = nullptr;   // fields and transforms of the energy transfer
