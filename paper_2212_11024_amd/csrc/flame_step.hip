@@ -16,7 +16,7 @@
 //     256 consecutive nodes; its arrays are addressed through buffer resources when every array
 //     ends at least 16 bytes below 4 GiB, otherwise through 64-bit global addresses (bitwise the
 //     same step either way).
-//   step_zmarch - stencil J: a workgroup owns a 64 x 8 tile of (x, y) and marches along z. It
+//   step_zmarch - stencil J: a workgroup owns a 64 x 8 (or 4) tile of (x, y) and marches along z. It
 //     keeps the field fluctuation b of three consecutive planes in LDS (computed once per node
 //     from that node's own magnetic populations, which it holds in registers for the next
 //     iteration) plus, for each plane, the one-node ring around the tile (computed one plane
@@ -220,19 +220,27 @@ __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
 
 // ------------------------------------------------------------------ stencil-route kernel
 // Tile of the stencil kernel (rows per tile overridable at build time): 64 x 8. The ring and the
-// lines that tiles share fall with the tile's height: 64 x 4 runs 2-8% slower at 256^3 and above
-// (FP32 256^3 3.17 against 3.03 ms for two steps, FP64 6.16 against 5.65, FP16 2.06 against 1.88),
-// 64 x 12 slower in FP32.
+// lines that tiles share fall with the tile's height: 64 x 4 runs 4-8% slower in FP32 and 11% in FP16 at
+// 256^3 (two steps: FP32 3.15 against 2.99 ms, FP16 1.85 against 1.67) and in FP64 3-4% slower at 96^3, 200^3
+// and, between two lattices, 256^3; 64 x 12 is slower in FP32. Eight rows are 512 threads of at most 256
+// registers, which some FP64 instantiations exceed. Four rows there: in the odd in-place BGK step, which
+// needs 302 (8 rows: 184 bytes of private memory; 96^3 234 against 190 us, 200^3 1805 against 1549,
+// 256^3 3191 against 2830), and in the state-saving steps (128^3 518 against 488 us, 64^3 66 against 58, 256^3 4.2
+// against 4.3 ms). The odd central one spills 4 registers at eight rows (128^3 327 us either way).
 #ifndef FLAME_TY
 #define FLAME_TY 8
 #endif
 constexpr int kTX = 64;
-constexpr int kTY = FLAME_TY;
+template <typename S, bool FAA, int PAR, bool SAVE, int MODEL>
+constexpr int tile_rows() {
+  return sizeof(S) == 8 && (SAVE || (FAA && PAR == 1 && (MODEL & kModelBGK) != 0)) ? 4 : FLAME_TY;
+}
 
 template <typename S, bool FAA, int PAR, bool SAVE, int MODEL>
-__global__ __launch_bounds__(kTX * kTY) void step_zmarch(StepArgs<S> a) {
+__global__ __launch_bounds__((kTX * tile_rows<S, FAA, PAR, SAVE, MODEL>())) void step_zmarch(StepArgs<S> a) {
   using E = Enc<S>;
   using R = typename E::R;
+  constexpr int kTY = tile_rows<S, FAA, PAR, SAVE, MODEL>();
   // b of the tile plus its one-node ring for a rolling window of planes:
   // [plane slot][ly + 1][lx + 1][component]. Four slots: a slot is rewritten two iterations
   // after it was last read, so one barrier per plane separates every write from every read.
@@ -360,13 +368,18 @@ __global__ __launch_bounds__(kTX * kTY) void step_zmarch(StepArgs<S> a) {
   }
 }
 
-// Planes per workgroup of the stencil kernel, per_cu workgroups resident on a compute unit (its
-// registers hold two in FP32 and FP16, one in FP64). With 32 planes everywhere 64^3 FP32 ran 32
-// workgroups and took 295 us for two steps against 52, 128^3 509 against 366, 32^3 275 against
-// 31; at 256^3 64 planes are the best (FP32 2.98 against 3.02 ms for 32 and 3.09 for 8, FP64 5.62, 5.75, 5.92).
-static int zchunk_planes(const flame_ctx* c, int per_cu) {
-  return march_planes(static_cast<int64_t>((c->p.nx + kTX - 1) / kTX) * ((c->p.ny + kTY - 1) / kTY), c->p.nz,
-                      static_cast<int64_t>(c->cus) * per_cu, 64);
+// With 32 planes per workgroup everywhere 64^3 FP32 ran 32 workgroups and took 295 us for two steps
+// against 52, 128^3 425 against 330, 32^3 275 against 24. FP32 and FP16 registers hold two
+// workgroups on a compute unit, those of FP64 one.
+template <typename S, bool FAA, int PAR, bool SAVE, int MODEL>
+static void launch_zmarch(const flame_ctx* c, StepArgs<S> a) {
+  constexpr int ty = tile_rows<S, FAA, PAR, SAVE, MODEL>();
+  constexpr int per_cu = sizeof(S) == 8 ? 1 : 2;
+  const int tiles = ((a.nx + kTX - 1) / kTX) * ((a.ny + ty - 1) / ty);
+  a.zchunk = c->zchunk > 0 ? std::min(a.nz, c->zchunk)
+                           : std::min(a.nz, march_planes(tiles, a.nz, static_cast<int64_t>(c->cus) * per_cu, 64));
+  const dim3 grid(static_cast<unsigned>(tiles) * ((a.nz + a.zchunk - 1) / a.zchunk));
+  hipLaunchKernelGGL((step_zmarch<S, FAA, PAR, SAVE, MODEL>), grid, dim3(kTX, ty, 1), 0, c->stream, a);
 }
 
 template <typename S, bool SAVE, int MODEL, Addr A>
@@ -401,14 +414,9 @@ template <typename S, bool SAVE, int MODEL>
 static void launch_model(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>& a) {
   const int par = c->parity;
   if (c->p.jmode == FLAME_J_STENCIL) {
-    const dim3 grid(((c->p.nx + kTX - 1) / kTX) * ((c->p.ny + kTY - 1) / kTY) * ((c->p.nz + a.zchunk - 1) / a.zchunk));
-    const dim3 block(kTX, kTY, 1);
-    if (!s.fluid_aa)
-      hipLaunchKernelGGL((step_zmarch<S, false, 0, SAVE, MODEL>), grid, block, 0, c->stream, a);
-    else if (par == 0)
-      hipLaunchKernelGGL((step_zmarch<S, true, 0, SAVE, MODEL>), grid, block, 0, c->stream, a);
-    else
-      hipLaunchKernelGGL((step_zmarch<S, true, 1, SAVE, MODEL>), grid, block, 0, c->stream, a);
+    if (!s.fluid_aa) launch_zmarch<S, false, 0, SAVE, MODEL>(c, a);
+    else if (par == 0) launch_zmarch<S, true, 0, SAVE, MODEL>(c, a);
+    else launch_zmarch<S, true, 1, SAVE, MODEL>(c, a);
   } else {
     // Buffer resources wherever the arrays fit: about 100 vector instructions of address arithmetic less
     // (two steps on the same buffers: FP32 256^3 2.75 against 2.78 ms, 161 x 130 x 99 322 against 328 us, 64^3 AB
@@ -443,7 +451,6 @@ static hipError_t launch_typed(const flame_ctx* c, const SetPtrs& s, size_t stri
   a.k.omega_b = R(c->omega_b);
   a.k.alpha = R(c->p.d_i);
   for (int i = 0; i < 3; ++i) a.k.b0[i] = R(c->p.b0[i]);
-  a.zchunk = c->p.jmode == FLAME_J_STENCIL ? std::min(c->p.nz, c->zchunk > 0 ? c->zchunk : zchunk_planes(c, sizeof(R) == 8 ? 1 : 2)) : 1;
   const int model = step_model(c->p);
   if constexpr (SAVE) {
     // the state-saving steps serve the adjoint, which is built for the paper's model only
