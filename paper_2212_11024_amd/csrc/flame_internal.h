@@ -167,6 +167,14 @@ inline int march_planes(int64_t tiles, int nz, int64_t resident, int most) {
   return best;
 }
 
+// Whether the curl-stencil step runs one workgroup on a compute unit where its registers allow two (the even
+// and two-lattice steps in FP32 and FP16). Two are a loss in FP32 unless forcing is read, which leaves
+// more to wait for (two steps, two workgroups against one: 200^3 1749 against 1678 us, 240^3 2585 against 2400,
+// 256^3 3020 against 2975 and between two lattices 2820 against 2625, 352^3 7750 against 7240, 384^3 9745
+// against 9390, 512^3 23.3 against 22.6 ms; 160^3 709 against 714 us). Forced FP32 steps keep two (even
+// step 160^3 355 against 404 us, 320^3 2735 against 2780), as do those of FP16 (256^3 1666 against 1696).
+inline bool one_group_per_cu(const flame_params& p) { return p.storage == FLAME_F32 && !p.force_u && !p.force_b; }
+
 // Threads per block of the node-local kernels: a row of nx nodes rounded up to whole wavefronts, at
 // most 256 (their launch bound), whatever FLAME_ROW_THREADS asks for. The blocks of the kernels that
 // split the grid by linear node index need not hold whole rows; there short rows only make blocks

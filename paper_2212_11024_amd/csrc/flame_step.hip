@@ -369,17 +369,20 @@ __global__ __launch_bounds__((kTX * tile_rows<S, FAA, PAR, SAVE, MODEL>())) void
 }
 
 // With 32 planes per workgroup everywhere 64^3 FP32 ran 32 workgroups and took 295 us for two steps
-// against 52, 128^3 425 against 330, 32^3 275 against 24. FP32 and FP16 registers hold two
-// workgroups on a compute unit, those of FP64 one.
+// against 50, 128^3 425 against 325, 32^3 275 against 24. Where one workgroup is to run on a compute unit
+// (one_group_per_cu), LDS is reserved for it; the odd in-place step's registers hold one in any case.
+constexpr unsigned kOneGroupLds = 52000;   // beside the tile's 31680 bytes more than half of 160 KB
 template <typename S, bool FAA, int PAR, bool SAVE, int MODEL>
 static void launch_zmarch(const flame_ctx* c, StepArgs<S> a) {
   constexpr int ty = tile_rows<S, FAA, PAR, SAVE, MODEL>();
-  constexpr int per_cu = sizeof(S) == 8 ? 1 : 2;
+  const bool alone = one_group_per_cu(c->p);
+  const int per_cu = sizeof(S) == 8 || alone || (FAA && PAR == 1) ? 1 : 2;
   const int tiles = ((a.nx + kTX - 1) / kTX) * ((a.ny + ty - 1) / ty);
   a.zchunk = c->zchunk > 0 ? std::min(a.nz, c->zchunk)
                            : std::min(a.nz, march_planes(tiles, a.nz, static_cast<int64_t>(c->cus) * per_cu, 64));
   const dim3 grid(static_cast<unsigned>(tiles) * ((a.nz + a.zchunk - 1) / a.zchunk));
-  hipLaunchKernelGGL((step_zmarch<S, FAA, PAR, SAVE, MODEL>), grid, dim3(kTX, ty, 1), 0, c->stream, a);
+  hipLaunchKernelGGL((step_zmarch<S, FAA, PAR, SAVE, MODEL>), grid, dim3(kTX, ty, 1), alone ? kOneGroupLds : 0, c->stream,
+                     a);
 }
 
 template <typename S, bool SAVE, int MODEL, Addr A>

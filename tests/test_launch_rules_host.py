@@ -1,0 +1,28 @@
+"""The rules by which launches are shaped, on the host, at the sizes where both sides were timed."""
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2212_11024_amd import _lib as L
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def lr(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    out = str(tmp_path_factory.mktemp("lr") / "lr.so")
+    subprocess.run([hipcc, "-O2", "-std=c++17", "-fPIC", "-shared", "--offload-host-only", "-x", "hip",
+                    os.path.join(HERE, "hostcheck", "launch_rules.hip"), "-o", out], check=True, stderr=subprocess.DEVNULL)
+    return ctypes.CDLL(out)
+
+
+def test_unforced_fp32_stencil_steps_run_one_workgroup_per_compute_unit(lr):
+    assert [lr.lr_one_group_per_cu(s, f) for s in (L.FLAME_F32, L.FLAME_F64, L.FLAME_F16) for f in (0, 1)] == \
+        [1, 0, 0, 0, 0, 0]
