@@ -167,6 +167,26 @@ inline int march_planes(int64_t tiles, int nz, int64_t resident, int most) {
   return best;
 }
 
+// Whether the node-local step stores the lattice with the non-temporal hint; state: bytes of one lattice.
+//
+// Between two lattices: where both together are far beyond the 256 MB last-level cache, so that nothing
+// written is read from it again (161 x 130 x 99 FP32 156 against 161 us a step, 100^3 FP64 149 against 153);
+// below, the next step finds the lattice there (64^3 FP32 18.5 against 23.5 us, 48^3 FP64 16 against 20.5).
+//
+// In place: plain, because plain lines stay in L2 until the neighbouring wavefronts have filled those that
+// shifted stores share (two steps, plain against hinted: FP32 64^3 33 against 40.5 us, 112^3 188 against 203,
+// 132^3 372 against 386, 160^3 657 against 708, 200^3 1250 against 1337; FP64 88^3 161 against 182, 112^3 446
+// against 455, 200^3 2460 against 2615; FP16 160^3 342 against 350). Except for FP32 and FP64 states a
+// little larger than the cache, of which the hint leaves the part that is read next (FP32 122^3 282 against
+// 265, 128^3 316 against 310, 161 x 130 x 99 322 against 318, 64 x 64 x 512 319 against 314; FP64 96^3 250
+// against 235, 100^3 300 against 272, 104^3 353 against 346). The ends: FP32 118^3 (301 MiB) 235 against 245
+// and 130^3 (402 MiB) 349 against 358, FP64 94^3 (304 MiB) 226 against 228 and 106^3 (436 MiB) as fast either way.
+constexpr size_t kMiB = size_t(1) << 20;
+inline bool nt_stores(bool two_lattices, size_t value_bytes, size_t state) {
+  if (two_lattices) return 2 * state > 384 * kMiB;
+  return value_bytes > 2 && state > 310 * kMiB && state <= (value_bytes == 4 ? 396 : 416) * kMiB;
+}
+
 // Whether the curl-stencil step runs one workgroup on a compute unit where its registers allow two (the even
 // and two-lattice steps in FP32 and FP16). Two are a loss in FP32 unless forcing is read, which leaves
 // more to wait for (two steps, two workgroups against one: 200^3 1749 against 1678 us, 240^3 2585 against 2400,

@@ -394,23 +394,23 @@ static void launch_local(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>
   // 20.6 ms for two steps, 384^3 9.42 -> 9.33 ms; at 256^3 and below, where it costs 0 to 30%, and in
   // FP16 and FP64, whose registers already bound the blocks, there is no limit).
   const unsigned lds = sizeof(S) == 4 && c->n >= kFewBlocksNodes ? kFewBlocksLds : 0;
-  // Non-temporal stores where what is written cannot be read back from a cache: beside a state that is
-  // written out (128^3 FP32), and between two lattices of more than 384 MB together (161 x 130 x 99 FP32
-  // 156 against 161 us a step, 100^3 FP64 149 against 153). Otherwise plain ones: below that size the
-  // next step finds the lattice in the last-level cache (64^3 FP32 18.5 against 23.5 us, 48^3 FP64 16 against
-  // 20.5), and in place they stay in L2 until the neighbouring wavefronts have filled the lines that
-  // shifted stores share (64^3 FP32 40.5 -> 33 us for two steps, 512^3 FP64 35.8 -> 35.5 ms; FP32 at
-  // 128^3 alone is slower, 318 -> 334 us).
-  if (!s.fluid_aa) {
-    if (SAVE || 2 * 48 * sizeof(S) * c->n > (size_t(384) << 20))
-      hipLaunchKernelGGL((step_local<S, false, false, 0, SAVE, MODEL, A, true>), grid, block, lds, c->stream, a);
-    else
-      hipLaunchKernelGGL((step_local<S, false, false, 0, SAVE, MODEL, A, false>), grid, block, lds, c->stream, a);
-  } else if (c->parity == 0) {
-    hipLaunchKernelGGL((step_local<S, true, true, 0, SAVE, MODEL, A, SAVE>), grid, block, lds, c->stream, a);
-  } else {
-    hipLaunchKernelGGL((step_local<S, true, true, 1, SAVE, MODEL, A, SAVE>), grid, block, lds, c->stream, a);
-  }
+  // Beside a state that is written out the hint is always set.
+  const bool nt = SAVE || nt_stores(!s.fluid_aa, sizeof(S), sizeof(S) * 48 * c->n);
+  auto go = [&](auto aa, auto par) {
+    constexpr bool AA = decltype(aa)::value;
+    constexpr int PAR = decltype(par)::value;
+    if constexpr (sizeof(S) > 2 || !AA || SAVE) {
+      if (nt) {
+        hipLaunchKernelGGL((step_local<S, AA, AA, PAR, SAVE, MODEL, A, true>), grid, block, lds, c->stream, a);
+        return;
+      }
+    }
+    if constexpr (!SAVE)
+      hipLaunchKernelGGL((step_local<S, AA, AA, PAR, SAVE, MODEL, A, false>), grid, block, lds, c->stream, a);
+  };
+  if (!s.fluid_aa) go(std::false_type{}, std::integral_constant<int, 0>{});
+  else if (c->parity == 0) go(std::true_type{}, std::integral_constant<int, 0>{});
+  else go(std::true_type{}, std::integral_constant<int, 1>{});
 }
 
 template <typename S, bool SAVE, int MODEL>

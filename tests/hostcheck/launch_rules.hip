@@ -11,3 +11,7 @@ int lr_one_group_per_cu(int storage, int forced) {
 }
 
 }  // extern "C"
+
+extern "C" int lr_nt_stores(int two_lattices, int value_bytes, int nx, int ny, int nz) {
+  return flame::nt_stores(two_lattices != 0, value_bytes, size_t(48) * value_bytes * nx * ny * nz);
+}

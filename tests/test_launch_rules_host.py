@@ -26,3 +26,13 @@ def lr(tmp_path_factory):
 def test_unforced_fp32_stencil_steps_run_one_workgroup_per_compute_unit(lr):
     assert [lr.lr_one_group_per_cu(s, f) for s in (L.FLAME_F32, L.FLAME_F64, L.FLAME_F16) for f in (0, 1)] == \
         [1, 0, 0, 0, 0, 0]
+
+
+@pytest.mark.parametrize("value,plain,hinted", [
+    (4, [(64,) * 3, (112,) * 3, (118,) * 3, (130,) * 3, (132,) * 3, (160,) * 3, (200,) * 3, (512,) * 3],
+     [(120,) * 3, (122,) * 3, (128,) * 3, (161, 130, 99), (64, 64, 512), (512, 64, 64)]),
+    (8, [(48,) * 3, (88,) * 3, (94,) * 3, (112,) * 3, (128,) * 3, (512,) * 3], [(96,) * 3, (98,) * 3, (100,) * 3, (104,) * 3]),
+    (2, [(128,) * 3, (152,) * 3, (160,) * 3, (256,) * 3], [])])
+def test_in_place_stores_take_the_side_that_was_faster(lr, value, plain, hinted):
+    assert [lr.lr_nt_stores(0, value, *g) for g in plain] == [0] * len(plain)
+    assert [lr.lr_nt_stores(0, value, *g) for g in hinted] == [1] * len(hinted)
