@@ -181,10 +181,34 @@ inline int march_planes(int64_t tiles, int nz, int64_t resident, int most) {
 // 265, 128^3 316 against 310, 161 x 130 x 99 322 against 318, 64 x 64 x 512 319 against 314; FP64 96^3 250
 // against 235, 100^3 300 against 272, 104^3 353 against 346). The ends: FP32 118^3 (301 MiB) 235 against 245
 // and 130^3 (402 MiB) 349 against 358, FP64 94^3 (304 MiB) 226 against 228 and 106^3 (436 MiB) as fast either way.
+//
+// Steps that also save their state write about as much again, 51 arrays that are not read soon, always with the
+// hint. Their lattice follows the same rule in place, with the hint up to larger FP64 states (two steps, plain
+// against hinted: FP32 96^3 157 against 217 us, 160^3 1037 against 1070, 200^3 1920 against 2034, 128^3 494 against
+// 481; FP64 64^3 97 against 108, 92^3 340 against 322, 108^3 598 against 540, 112^3 670 against 616, 120^3 823
+// against 822, 128^3 955 against 968, 200^3 3818 against 3958; FP16 96^3 112 against 143), and keeps it
+// between two lattices (FP32 256^3 3935 against 4012 us, 96^3 222 against 237).
 constexpr size_t kMiB = size_t(1) << 20;
-inline bool nt_stores(bool two_lattices, size_t value_bytes, size_t state) {
-  if (two_lattices) return 2 * state > 384 * kMiB;
-  return value_bytes > 2 && state > 310 * kMiB && state <= (value_bytes == 4 ? 396 : 416) * kMiB;
+inline bool nt_stores(bool two_lattices, bool save, size_t value_bytes, size_t state) {
+  if (two_lattices) return save || 2 * state > 384 * kMiB;
+  return value_bytes > 2 && state > 310 * kMiB && state <= (value_bytes == 4 ? 396 : save ? 640 : 416) * kMiB;
+}
+
+// LDS reserved by a block of the node-local step, so that fewer blocks share a compute unit and fewer rows
+// in flight keep the lines that shifted accesses share in L2. FP32 states from 6 GiB on (2^25 nodes): three
+// blocks of 256 threads instead of four to six (two steps, without and with: 336^3 6.07 and 5.92 ms, 384^3 8.88 and
+// 8.70, 448^3 14.3 and 13.9, 512^3 20.3 and 20.0; trace steps 512^3 16.76 and 16.70; at 256^3 2.67 and 2.75, at 288^3 3.76
+// and 3.69, 320^3 5.18 and 5.07, where the rule forgoes 2%). State-saving FP32 and FP16 steps, which
+// write 99 arrays, from 264 MiB on: two blocks (160^3 FP32 1037 and 976 us, 256^3 4.20 and 3.90 ms, 512^3 in place
+// 28.5 and 28.0; FP16 144^3 546 and 507 us, 256^3 2.96 and 2.59 ms; between two lattices FP32 256^3 3.94 and 3.84 ms,
+// FP16 192^3 1185 and 1114 us; below, FP32 112^3 269 and 278 us, FP16 128^3 246 and 283), but not in place with the
+// hint (FP32 128^3 481 and 497 us). FP64's registers bound its blocks.
+constexpr unsigned kThreeBlocksLds = 50000, kTwoBlocksLds = 78000;   // of the 160 KB of a compute unit
+inline unsigned reserved_lds(bool two_lattices, bool save, size_t value_bytes, size_t state) {
+  if (save)
+    return value_bytes < 8 && state > 264 * kMiB && (two_lattices || !nt_stores(false, true, value_bytes, state))
+               ? kTwoBlocksLds : 0;
+  return value_bytes == 4 && state >= 6144 * kMiB ? kThreeBlocksLds : 0;
 }
 
 // Whether the curl-stencil step runs one workgroup on a compute unit where its registers allow two (the even

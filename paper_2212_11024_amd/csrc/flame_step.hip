@@ -182,8 +182,6 @@ __device__ __forceinline__ void save_current(R* save, size_t n, uint32_t cell, c
 // between two lattices from 265 to 155 us, FP16 384^3 from 2.78 to 2.28 ms and FP64 32^3 from 10.6 to 8.7 us.
 constexpr int kLocalThreads = 256;
 static_assert(kLocalThreads == kRowThreadsMax, "blocks are launched with up to kRowThreadsMax threads");
-constexpr size_t kFewBlocksNodes = size_t(1) << 25;
-constexpr unsigned kFewBlocksLds = 50000;   // of the 160 KB of a compute unit
 
 template <typename S, bool FAA, bool MAA, int PAR, bool SAVE, int MODEL, Addr A, bool NT>
 __global__ __launch_bounds__(kLocalThreads) void step_local(StepArgs<S> a) {
@@ -389,23 +387,19 @@ template <typename S, bool SAVE, int MODEL, Addr A>
 static void launch_local(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>& a) {
   const dim3 block(a.shape.threads, 1, 1);
   const dim3 grid(a.shape.blocks);
-  // FP32 grids far beyond the 256 MB last-level cache: LDS is reserved so that three blocks share a
-  // compute unit instead of four to six. Fewer rows in flight keep the shared lines in L2 (512^3 21.2 ->
-  // 20.6 ms for two steps, 384^3 9.42 -> 9.33 ms; at 256^3 and below, where it costs 0 to 30%, and in
-  // FP16 and FP64, whose registers already bound the blocks, there is no limit).
-  const unsigned lds = sizeof(S) == 4 && c->n >= kFewBlocksNodes ? kFewBlocksLds : 0;
-  // Beside a state that is written out the hint is always set.
-  const bool nt = SAVE || nt_stores(!s.fluid_aa, sizeof(S), sizeof(S) * 48 * c->n);
+  const size_t state = sizeof(S) * 48 * c->n;
+  const bool two = !s.fluid_aa, nt = nt_stores(two, SAVE, sizeof(S), state);
+  const unsigned lds = reserved_lds(two, SAVE, sizeof(S), state);
   auto go = [&](auto aa, auto par) {
     constexpr bool AA = decltype(aa)::value;
     constexpr int PAR = decltype(par)::value;
-    if constexpr (sizeof(S) > 2 || !AA || SAVE) {
+    if constexpr (sizeof(S) > 2 || !AA) {
       if (nt) {
         hipLaunchKernelGGL((step_local<S, AA, AA, PAR, SAVE, MODEL, A, true>), grid, block, lds, c->stream, a);
         return;
       }
     }
-    if constexpr (!SAVE)
+    if constexpr (AA || !SAVE)
       hipLaunchKernelGGL((step_local<S, AA, AA, PAR, SAVE, MODEL, A, false>), grid, block, lds, c->stream, a);
   };
   if (!s.fluid_aa) go(std::false_type{}, std::integral_constant<int, 0>{});

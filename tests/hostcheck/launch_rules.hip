@@ -12,6 +12,10 @@ int lr_one_group_per_cu(int storage, int forced) {
 
 }  // extern "C"
 
-extern "C" int lr_nt_stores(int two_lattices, int value_bytes, int nx, int ny, int nz) {
-  return flame::nt_stores(two_lattices != 0, value_bytes, size_t(48) * value_bytes * nx * ny * nz);
+static size_t state(int value_bytes, int nx, int ny, int nz) { return size_t(48) * value_bytes * nx * ny * nz; }
+extern "C" int lr_nt_stores(int two_lattices, int save, int value_bytes, int nx, int ny, int nz) {
+  return flame::nt_stores(two_lattices != 0, save != 0, value_bytes, state(value_bytes, nx, ny, nz));
+}
+extern "C" unsigned lr_reserved_lds(int two_lattices, int save, int value_bytes, int nx, int ny, int nz) {
+  return flame::reserved_lds(two_lattices != 0, save != 0, value_bytes, state(value_bytes, nx, ny, nz));
 }
