@@ -135,10 +135,6 @@ __device__ __forceinline__ bool own_cell(const GridShape& g, uint32_t& cell) {
   return cell < g.n;
 }
 
-// Buffer addressing is used when every array the kernel touches ends at least 16 bytes below
-// 4 GiB, so that no access can meet the range limit whichever byte of it the hardware checks.
-inline bool buffer_fits(size_t array_bytes) { return array_bytes <= (size_t(1) << 32) - 16; }
-
 }  // namespace flame
 
 #endif

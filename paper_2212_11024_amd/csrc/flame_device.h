@@ -403,7 +403,7 @@ FLAME_HD void populate_reverse(R (&l)[kQ], R rho, const R (&U)[3], const R (&Q)[
 // (M(B) - M(b0)) : (c c - c_s^2 I), E_i = prod_a (1 + e_a), M(B) = |B|^2/2 I - B B.
 //
 // The tensor-product transforms above form the 27 directions: against one polynomial evaluation per
-// direction they take the step from 1073 to 703 vector instructions and 265 to 172 registers (FP64),
+// direction they take the step from 1073 to 707 vector instructions and 265 to 172 registers (FP64, odd in place),
 // the FP16 step at 384^3 from 5.55 to 5.04 ms and FP64 at 512^3 from 37.1 to 35.8 ms for an even
 // and an odd step, and their FP32 error against FP64 is 30% smaller. (The second template argument has
 // no effect.)

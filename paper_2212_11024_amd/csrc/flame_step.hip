@@ -415,9 +415,10 @@ static void launch_model(const flame_ctx* c, const SetPtrs& s, const StepArgs<S>
     else if (par == 0) launch_zmarch<S, true, 0, SAVE, MODEL>(c, a);
     else launch_zmarch<S, true, 1, SAVE, MODEL>(c, a);
   } else {
-    // Buffer resources wherever the arrays fit: about 100 vector instructions of address arithmetic less
-    // (two steps on the same buffers: FP32 256^3 2.75 against 2.78 ms, 161 x 130 x 99 322 against 328 us, 64^3 AB
-    // 35.7 against 36.2 us, 320^3 alone 5.16 against 5.12 ms).
+    // Buffer resources wherever the arrays fit: 150 to 170 vector instructions of address arithmetic less
+    // (FP32 in place 736 and 825 with global addresses, 587 and 660 with these; two steps on the same buffers:
+    // FP32 256^3 2.75 against 2.78 ms, 161 x 130 x 99 322 against 328 us, 64^3 AB 35.7 against 36.2 us, 320^3 alone
+    // 5.16 against 5.12 ms).
     const bool arith_arrays = SAVE || c->p.force_u || c->p.force_b;
     if (!c->global_addr && buffer_addressing_ok(c->p, arith_arrays)) {
       launch_local<S, SAVE, MODEL, Addr::Buffer>(c, s, a);
