@@ -40,13 +40,13 @@ def spectral_gradient(v: torch.Tensor) -> torch.Tensor:
             f[n // 2] = 0.0           # the Nyquist mode has no well-defined derivative
         return f
 
-    # real transforms (half the spectrum), one axis at a time: complex ones took 0.26 ms at 48^3 and 8.7 ms at
-    # 256^3 (these 0.21 and 5.3) and 290 to 360 bytes a node of memory at the peak (these 170); all nine
-    # derivatives in one batch take 0.18 and 5.3 ms, but 320 bytes and 0.14 ms more with the backward at 48^3.
-    # The stack makes the result dense, whatever the strides that a transform returns.
+    # real transforms (half the spectrum), the three axes back in one batch: with complex ones and one
+    # inverse per axis the gradients took 0.8 ms of a 2.1 ms rollout of 12 steps at 48^3 and, at the peak, 290 to
+    # 360 bytes a node (these 315 to 320). One inverse per axis holds 170, but its launches add 0.2 ms to that rollout.
     vh = torch.fft.rfftn(v, dim=(1, 2, 3))
     ik = (k(nx, torch.fft.rfftfreq).view(1, 1, -1), k(ny).view(1, ny, 1), k(nz).view(nz, 1, 1))
-    return torch.stack([torch.fft.irfftn(1j * ka * vh, s=(nz, ny, nx), dim=(1, 2, 3)) for ka in ik])
+    g = torch.fft.irfftn(torch.stack([1j * ka * vh for ka in ik]), s=(nz, ny, nx), dim=(2, 3, 4))
+    return g.contiguous()         # the transform's output may have any strides
 
 
 def shell_spectrum(v: torch.Tensor, nshells: int) -> torch.Tensor:
