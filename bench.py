@@ -43,13 +43,13 @@ HBM_PEAK_GBPS = 8000.0        # MI355X HBM3E peak
 # a plain copy (see the traffic summary named below). Valid only for the kernel source it was
 # measured on: reported as null once the fingerprint of the kernel sources changes.
 TRAFFIC_RECORDS = {
-    ("f32", "moment", "aa"): {"fingerprint": "19d03cad1662a299", "GB_per_launch": 55.0,
+    ("f32", "moment", "aa"): {"fingerprint": "99373b547f2d6b8c", "GB_per_launch": 55.0,
                         "profile": "profiles/traffic_step_f32_moment_512.md"},
-    ("f32", "stencil", "aa"): {"fingerprint": "19d03cad1662a299", "GB_per_launch": 65.1,
+    ("f32", "stencil", "aa"): {"fingerprint": "99373b547f2d6b8c", "GB_per_launch": 65.0,
                          "profile": "profiles/traffic_step_f32_stencil_512.md"},
-    ("f64", "moment", "aa"): {"fingerprint": "19d03cad1662a299", "GB_per_launch": 109.7,
+    ("f64", "moment", "aa"): {"fingerprint": "99373b547f2d6b8c", "GB_per_launch": 109.7,
                         "profile": "profiles/traffic_step_f64_moment_512.md"},
-    ("f32", "stencil", "ab"): {"fingerprint": "19d03cad1662a299", "GB_per_launch": 70.0,
+    ("f32", "stencil", "ab"): {"fingerprint": "99373b547f2d6b8c", "GB_per_launch": 70.0,
                                "profile": "profiles/traffic_step_f32_stencil_ab_512.md"},
 }
 
